@@ -162,7 +162,9 @@ dmas_status_t dmas_plan_desc_init(dmas_plan_desc_t *desc);
  * 64 microphones reads the tables (one microphone ahead, or a block of
  * offsets at a time), DMAS_RING_SHARING=0/1 whether a kernel reading a block
  * of offsets at a time keeps the envelope rings in the LDS region of the
- * channel windows, DMAS_LOG prints the plan's choices and errors to stderr. */
+ * channel windows, DMAS_ENVELOPE_PASSES=1/2 whether dmas_envelope (without
+ * decimation) filters in the beamforming kernel or in a pass of its own over
+ * the RF image in d_env, DMAS_LOG prints the plan's choices and errors to stderr. */
 dmas_status_t dmas_plan_create(const dmas_plan_desc_t *desc, dmas_plan_t *out);
 
 /* Release a plan and its device memory. NULL is a no-op. Work queued with
@@ -187,9 +189,11 @@ dmas_status_t dmas_plan_query(dmas_plan_t plan, dmas_plan_info_t *info);
 dmas_status_t dmas_beamform(dmas_plan_t plan, const void *d_x, float *d_y,
                             float in_scale, void *stream);
 
-/* DMAS-n (+CF) image followed by envelope detection in the same kernel:
- * writes d_env (D x ceil(T/k) FP32, device; k = env_decimation). Arguments,
- * root plane and errors as for dmas_beamform. */
+/* DMAS-n (+CF) image followed by envelope detection, in the same kernel or
+ * (plans without decimation, where it is faster) in a second one that filters
+ * the RF image in d_env in place: writes d_env (D x ceil(T/k) FP32, device;
+ * k = env_decimation). Arguments, root plane and errors as for
+ * dmas_beamform. */
 dmas_status_t dmas_envelope(dmas_plan_t plan, const void *d_x, float *d_env,
                             float in_scale, void *stream);
 

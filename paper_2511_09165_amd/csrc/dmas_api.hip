@@ -245,6 +245,45 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
     }
 }
 
+// The same without an envelope: segments share nothing, so a cut costs only
+// the workgroup's setup.
+void choose_rf_segments(int T, int num_tiles, int64_t slots, int fixed, int *seg, int *nseg)
+{
+    int s = (fixed + 31) & ~31;
+    if (fixed <= 0) {
+        int chunks = 3;
+        while (chunks > 1 && (int64_t)num_tiles * ((T + chunks * dmas::kChunk - 1) / (chunks * dmas::kChunk)) < 4 * slots)
+            --chunks;
+        s = chunks * dmas::kChunk;
+    }
+    *seg = s;
+    *nseg = (T + s - 1) / s;
+}
+
+// Whether an envelope call runs as two passes: the RF image into the output,
+// then the filter over its rows in place (the same bits as the fused kernel).
+// The fused kernel's workgroups each walk long segments (a cut recomputes the
+// filter's halo), so a launch of few device rounds ends unevenly, and starts
+// with every workgroup staging and summing in step; RF workgroups take 1-3
+// chunks. Measured over frames of 8-780 microphones: the fused form loses
+// about a fifth of the RF time below three device rounds, while the second
+// pass costs 0.6 ps per pixel more than the fused filter (2.0 against 1.4 at
+// 4186 x 16384 pixels) and a launch of about 4 us. 64 microphones, 1035 x 8192
+// at order 3: 133 -> 121 us; 517 microphones, 361 x 4096 at order 2: 225 ->
+// 166 us; but 32 microphones, 4186 x 16384 at order 5 (5.5 rounds): 528 ->
+// 558 us, and 30 microphones, 145 x 14067 at order 3: 34 -> 46 us. RF
+// launches of fewer than two workgroups per compute unit are no better spread.
+bool two_pass_pays(const dmas_plan_s *p)
+{
+    const double pixels = (double)p->D * p->T;
+    const double slots = p->order + 2 + (p->linear ? 6 : 0);           // VALU slots per microphone and pixel
+    const double rf = pixels * p->M * slots / 33e12 * (p->compensated ? 2 : 1);   // seconds
+    const int64_t wgs_rf = (int64_t)p->num_tiles * p->nseg_rf;
+    const int64_t wgs_env = (int64_t)p->num_tiles * p->nseg_env;
+    return wgs_rf >= 2 * (int64_t)p->cus && wgs_env < 3 * (int64_t)p->cus * std::max(1, p->occ_env) &&
+           0.2 * rf > 0.6e-12 * pixels + 4e-6;
+}
+
 // Host estimate of fs*tau (tiling heuristics only; the kernels compute their own).
 double host_steer(const double *r, const double *v, bool nearfield, double fs, double c)
 {
@@ -464,8 +503,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
         // every element the kernel reads is written here first: nothing needs clearing
         e = dmas::stage_roots(plan, d_x, fixed, st);
         if (e != hipSuccess) return hip_fail(e, "root-plane launch");
-        const dmas::KernelParams kp = dmas::make_params(plan, d_x, fixed, d_out, in_scale, env);
-        e = dmas::launch_plan(plan->order, &kp, dmas::shape_of(plan, env), st);
+        e = dmas::launch_image(plan, d_x, fixed, d_out, in_scale, env, st);
         if (e == hipErrorNotSupported)
             return fail(DMAS_ERR_UNSUPPORTED, "no kernel for order %d cf=%d env=%d near=%d accumulate=%d",
                         plan->order, (int)plan->cf, (int)env, (int)plan->nearfield, (int)plan->compensated);
@@ -484,9 +522,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
             return hip_fail(e, "root-plane launch");
         }
     }
-    const dmas::KernelParams kp = dmas::make_params(plan, d_x, plane, d_out, in_scale, env);
-    const dmas::LaunchShape ls = dmas::shape_of(plan, env);
-    e = dmas::launch_plan(plan->order, &kp, ls, st);
+    e = dmas::launch_image(plan, d_x, plane, d_out, in_scale, env, st);
     if (plane) {
         const hipError_t ef = hipFreeAsync(plane, st);
         if (e == hipSuccess) e = ef;
@@ -563,6 +599,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     dmas_plan_s *p = new (std::nothrow) dmas_plan_s();
     if (!p) return fail(DMAS_ERR_OUT_OF_MEMORY, "host allocation failed");
     p->device = dev;
+    p->cus = prop.multiProcessorCount;
     p->M = M;
     p->T = T;
     p->D = D;
@@ -798,9 +835,11 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         if (env)
             choose_segments(T, p->num_tiles, H, slots, seg_override, &p->seg_env, &p->nseg_env);
         else
-            choose_segments(T, p->num_tiles, 0, slots, seg_override, &p->seg_rf, &p->nseg_rf);
+            choose_rf_segments(T, p->num_tiles, slots, seg_override, &p->seg_rf, &p->nseg_rf);
         if (env) p->occ_env = blocks; else p->occ_rf = blocks;
     }
+    p->two_pass = decim == 1 && two_pass_pays(p);
+    if (const char *ep = std::getenv("DMAS_ENVELOPE_PASSES")) p->two_pass = decim == 1 && std::atoi(ep) == 2;
     if ((int64_t)p->num_tiles * std::max(p->nseg_rf, p->nseg_env) > INT32_MAX) {
         plan_free(p);
         return fail(DMAS_ERR_UNSUPPORTED, "grid too large");

@@ -1,0 +1,192 @@
+// Envelope filter as a pass of its own over an RF image that is already in
+// the output buffer: env[t] = sum_k h[k] |y[t + H - k]|, y = 0 outside [0, T),
+// row by row and in place.
+//
+// The same 16 x 16 Toeplitz products in FP32 on the matrix cores, in the same
+// K order, as the beamformer's fused epilogue (dmas_kernel.hpp): an output's
+// products depend on its time index modulo 16 only, so both forms give the
+// same bits.
+//
+// Bound: HBM (each sample read and written once) and the matrix cores, whose
+// FP32 products do not run beside one another's loads well: 4186 x 16384
+// samples take 139 us (3.9 TB/s), 94 us with the products left out (5.8 TB/s;
+// a large copy reaches 5.1-5.4) and 80 us for the products alone. Loads one
+// step ahead and barriers that wait for LDS only brought it there from 190 us.
+#include "dmas_internal.hpp"
+
+namespace dmas {
+
+namespace {
+
+constexpr int kRowThreads = 256;
+constexpr int kRowWaves = kRowThreads / kWaveSize;
+constexpr int kRowBlock = 2048;   // outputs of one walk step
+static_assert(kRowBlock % (kChunk * kRowWaves) == 0, "each wave takes whole output blocks");
+
+// LDS window of a walk step: |y| of indices [0, kRowBlock + 2H) and zeros up
+// to the last index that the FIR's K steps read. Index i lies in plane i % 4
+// at i / 4: a lane's operand of K steps 4q .. 4q + 3 is then 16 consecutive
+// bytes (one ds_read_b128 instead of four 4-byte reads), and the planes lie
+// 16 banks apart, so that both those reads and the element-wise fill, 64
+// consecutive indices a wave, fall on distinct banks.
+__host__ __device__ constexpr int row_logical(int H) { return kRowBlock + 2 * H + 24; }
+__host__ __device__ constexpr int row_plane(int H) { return ((row_logical(H) / 4 + 1 + 63) & ~63) + 16; }
+__host__ __device__ constexpr int row_floats(int H) { return 4 * row_plane(H); }
+// Output staging of a wave whose rows are not 16-byte aligned.
+constexpr int kRowStage = kChunk;
+
+// Barrier for LDS traffic alone: the workgroup's global loads and stores in
+// flight (the next step's samples, this step's outputs) are not waited for.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// A workgroup walks whole rows, blockIdx.x and every gridDim.x-th after it, in
+// steps of kRowBlock outputs, and loads the next step's samples while it works
+// on this one's. The step at o0 holds |y| of [o0 - H, o0 + kRowBlock + H) (its
+// first 2H values kept from the step before) and stores [o0, o0 + kRowBlock);
+// the samples loaded ahead start at o0 + kRowBlock + H or in another row, so
+// no output is stored over a sample that is still to be loaded.
+// KS: K steps whose taps a lane keeps in registers (0: read per block).
+template <int KS>
+__global__ void __launch_bounds__(kRowThreads, 8)
+envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, int D, int T, int L)
+{
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    extern __shared__ float smem[];
+    const int H = (L - 1) / 2;
+    const int plane = row_plane(H);
+    float *win = smem;
+    float *stage = smem + row_floats(H);
+    float *tap_lds = stage + kRowWaves * kRowStage;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
+    const int g = lane >> 4, c = lane & 15;
+    const int ks = env_ksteps(H);
+    auto at = [&](int i) { return (i & 3) * plane + (i >> 2); };
+
+    // new samples of a step: t = o0 + H + j * kRowThreads + tid; the first step
+    // of a row also has samples 0 .. H - 1 (H < kRowThreads)
+    constexpr int kLoads = kRowBlock / kRowThreads;
+    float v[kLoads], head = 0.0f;
+    auto fetch = [&](int d, int o0) {
+        const float *src = img + (size_t)d * (size_t)T;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            const int t = o0 + H + j * kRowThreads + tid;
+            v[j] = t < T ? src[t] : 0.0f;
+        }
+        if (o0 == 0) head = tid >= H && tid < 2 * H && tid - H < T ? src[tid - H] : 0.0f;
+    };
+    int d = blockIdx.x, o0 = 0;
+    if (d < D) fetch(d, 0);
+
+    for (int j = tid; j < env_taps_len(H); j += kRowThreads) {
+        const int k = j - kTapLead;   // reversed: entry kTapLead + k holds h[2H - k]
+        tap_lds[j] = (k >= 0 && k <= 2 * H) ? taps[2 * H - k] : 0.0f;
+    }
+    for (int i = kRowBlock + 2 * H + tid; i < row_logical(H); i += kRowThreads) win[at(i)] = 0.0f;
+    lds_barrier();
+    const float *ha = tap_lds + kTapLead + g - c;   // hr[m - i] of K step kk at ha[4 kk]
+    float a[KS > 0 ? KS : 1];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) a[kk] = kk < ks ? ha[4 * kk] : 0.0f;
+
+    while (d < D) {
+        // window index i holds |y[o0 - H + i]|
+        float keep = __builtin_fabsf(head);            // indices 0 .. 2H - 1 (2H < kRowThreads)
+        if (o0 > 0) {
+            if (tid < 2 * H) keep = win[at(kRowBlock + tid)];
+            lds_barrier();
+        }
+        if (tid < 2 * H) win[at(tid)] = keep;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) win[at(2 * H + j * kRowThreads + tid)] = __builtin_fabsf(v[j]);
+        lds_barrier();
+        float *row = img + (size_t)d * (size_t)T;
+        const int o = o0;
+        o0 += kRowBlock;
+        if (o0 >= T) {
+            o0 = 0;
+            d += gridDim.x;
+        }
+        if (d < D) fetch(d, o0);
+
+        for (int b = wave * kChunk; b < min(kRowBlock, T - o); b += kRowWaves * kChunk) {
+            // outputs o + b + q, q = 16j + i: F[i][j] = sum_m hr[m - i] r[16j + m], r = window
+            // from b; lane l supplies r[16c + 4kk + g] and receives the outputs 16c + 4g ..+3
+            const v4f *rq = reinterpret_cast<const v4f *>(win + g * plane + (b >> 2) + 4 * c);
+            v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (KS > 0) {
+#pragma unroll
+                for (int q = 0; q < (KS + 3) / 4; ++q) {
+                    if (4 * q >= ks) break;
+                    const v4f r = rq[q];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (4 * q + u >= ks) break;
+                        if (u & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * q + u], r[u], e1, 0, 0, 0);
+                        else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * q + u], r[u], e0, 0, 0, 0);
+                    }
+                }
+            } else {
+                for (int q = 0; 4 * q < ks; ++q) {
+                    const v4f r = rq[q];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (4 * q + u >= ks) break;
+                        if (u & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[16 * q + 4 * u], r[u], e1, 0, 0, 0);
+                        else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[16 * q + 4 * u], r[u], e0, 0, 0, 0);
+                    }
+                }
+            }
+            const v4f e = e0 + e1;
+            const int t0 = o + b;
+            const int t = t0 + 16 * c + 4 * g;
+            if ((reinterpret_cast<uintptr_t>(row) & 15) == 0) {   // wave-uniform
+                float *dst = row + t;
+                if (t + 3 < T) {
+                    __builtin_nontemporal_store(e, reinterpret_cast<v4f *>(dst));
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (t + u < T) __builtin_nontemporal_store(e[u], dst + u);
+                }
+            } else {
+                // rows off the 16-byte grid: through LDS, so that a wave stores 256
+                // consecutive bytes at a time instead of 4-byte pieces 16 apart
+                float *st = stage + wave * kRowStage;
+                *reinterpret_cast<v4f *>(st + 16 * c + 4 * g) = e;
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int q = lane + kWaveSize * u;
+                    if (t0 + q < T) __builtin_nontemporal_store(st[q], row + t0 + q);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        lds_barrier();   // the window is read before the next step fills it
+    }
+}
+
+}  // namespace
+
+hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int L, int cus, hipStream_t stream)
+{
+    const int H = (L - 1) / 2;
+    const size_t lds = sizeof(float) * (size_t)(row_floats(H) + kRowWaves * kRowStage + env_taps_len(H));
+    // workgroups for eight a CU (their LDS and registers allow eight)
+    const unsigned grid = (unsigned)(D < 8 * cus ? D : 8 * cus);
+    auto kern = env_ksteps(H) <= 20 ? envelope_rows_kernel<20> : envelope_rows_kernel<0>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, stream, img, taps, D, T, L);
+    return hipGetLastError();
+}
+
+}  // namespace dmas

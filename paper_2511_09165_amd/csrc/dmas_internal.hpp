@@ -170,6 +170,10 @@ hipError_t launch_batch_order8(const BatchParams &, bool, bool, bool, int, unsig
 // count = M * T channel samples of x (storage type dtype), in FP32.
 hipError_t launch_roots(int order, int dtype, const void *x, float2 *plane, size_t count, hipStream_t stream);
 
+// Envelope filter of an RF image (D rows of T samples) in place, for the plan's
+// taps on the device (L of them, zero-padded); cus: compute units of the device.
+hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int L, int cus, hipStream_t stream);
+
 // Matched filter: out[i*T + t] = sum_{k<P} raw[i*T + t + k] * pulse[k].
 hipError_t launch_matched_filter(const float *raw, const float *pulse, int M, int T, int P, float *out,
                                  hipStream_t stream);

@@ -22,6 +22,7 @@ inline std::atomic<uint64_t> &plan_serials()
 struct dmas_plan_s {
     uint64_t serial = dmas::plan_serials().fetch_add(1);   // creation order
     int device = 0;
+    int cus = 0;           // its compute units
     int M = 0, T = 0, D = 0, order = 0;
     bool cf = true, nearfield = false, linear = false;
     bool roots = false;    // kernel reads a root plane (whole-sample delays, n >= 2)
@@ -38,6 +39,7 @@ struct dmas_plan_s {
     int halo = 0;
     int mic_block = 0;
     int row = 0;
+    bool two_pass = false; // envelope calls: RF image into the output, then the filter over it in place
     int seg_rf = 0, seg_env = 0;
     int nseg_rf = 0, nseg_env = 0;
     size_t lds_rf = 0, lds_env = 0;
@@ -134,5 +136,18 @@ void set_last_error(const char *msg);
 // Launch one plan (order dispatch); with kp == nullptr, report occupancy in *blocks.
 hipError_t launch_plan(int order, const KernelParams *kp, const LaunchShape &ls, hipStream_t st,
                        int *blocks = nullptr);
+
+// Launch the beamformer of one call and, for an envelope in two passes, the
+// filter over its image (d_plane filled before, in stream order).
+inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const float2 *d_plane, float *d_out,
+                               float in_scale, bool env, hipStream_t stream)
+{
+    const bool fused = env && !plan->two_pass;
+    const KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused);
+    hipError_t e = launch_plan(plan->order, &kp, shape_of(plan, fused), stream);
+    if (e == hipSuccess && env && !fused)
+        e = launch_envelope_rows(d_out, plan->d_taps, plan->D, plan->T, plan->fir_len, plan->cus, stream);
+    return e;
+}
 
 }  // namespace dmas
