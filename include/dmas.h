@@ -164,7 +164,10 @@ dmas_status_t dmas_plan_desc_init(dmas_plan_desc_t *desc);
  * of offsets at a time keeps the envelope rings in the LDS region of the
  * channel windows, DMAS_ENVELOPE_PASSES=1/2 whether dmas_envelope (without
  * decimation) filters in the beamforming kernel or in a pass of its own over
- * the RF image in d_env, DMAS_LOG prints the plan's choices and errors to stderr. */
+ * the RF image in d_env, DMAS_DIRECT_ROOTS=0/1 whether calls on a plan with
+ * tables take the signed roots while staging the channel windows instead of
+ * from a root plane (a choice made only where DMAS_RING_SHARING is not set),
+ * DMAS_LOG prints the plan's choices and errors to stderr. */
 dmas_status_t dmas_plan_create(const dmas_plan_desc_t *desc, dmas_plan_t *out);
 
 /* Release a plan and its device memory. NULL is a no-op. Work queued with
@@ -183,7 +186,8 @@ dmas_status_t dmas_plan_query(dmas_plan_t plan, dmas_plan_info_t *info);
  * plane of M x T (root, sample) FP32 pairs, which the beamformer then reads
  * in place of d_x; the plane is allocated and freed in stream order from a
  * device memory pool that the library keeps per device (M*T*8 bytes per call
- * in flight), so one plan may be used on several streams at once. Errors:
+ * in flight), so one plan may be used on several streams at once. Small frames
+ * take the same roots inside the beamformer and use no plane. Errors:
  * DMAS_ERR_INVALID_ARG (NULL pointers, in_scale, plan of another device),
  * DMAS_ERR_OUT_OF_MEMORY (plane allocation), DMAS_ERR_DEVICE (launch). */
 dmas_status_t dmas_beamform(dmas_plan_t plan, const void *d_x, float *d_y,

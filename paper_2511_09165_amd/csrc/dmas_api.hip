@@ -260,6 +260,21 @@ void choose_rf_segments(int T, int num_tiles, int64_t slots, int fixed, int *seg
     *nseg = (T + s - 1) / s;
 }
 
+// Whether a single call takes the roots while staging instead of reading them
+// from a root plane (the same bits). The plane costs a launch (2-3 us) and a
+// pool allocation and free around the call (about 15 us of host time, which
+// bounds calls whose kernels are shorter); without it a sample's root is taken
+// again in every window that holds it, work that grows with the pixels and
+// microphones. Measured (back to back): 8 microphones, 64 x 1024 at order 2
+// 26.4 -> 10.2 us, 19, 181 x 3001 at order 3 30.9 -> 12.0 us, 18, 351 x 7669
+// at order 6 (4.9e7 pixel-microphones) 30.1 -> 26.2 us, 30, 145 x 14067 at
+// order 3 (6.1e7) 33.9 -> 31.2 us, but 20, 2211 x 1836 at order 7 (8.1e7)
+// 61.8 -> 67.0 us and 25, 2450 x 3037 at order 3 (1.9e8) 42.5 -> 46.8 us.
+bool direct_roots_pay(const dmas_plan_s *p)
+{
+    return (double)p->M * p->D * p->T < 7e7;
+}
+
 // Whether an envelope call runs as two passes: the RF image into the output,
 // then the filter over its rows in place (the same bits as the fused kernel).
 // The fused kernel's workgroups each walk long segments (a cut recomputes the
@@ -498,11 +513,13 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
                         "dmas_envelope_noalloc",
                         need, plan->M, plan->T, (size_t)DMAS_NOALLOC_SCRATCH_BYTES);
         float2 *fixed = nullptr;
-        e = scratch_address(plan->device, &fixed);
-        if (e != hipSuccess) return hip_fail(e, "address of the fixed root-plane scratch");
-        // every element the kernel reads is written here first: nothing needs clearing
-        e = dmas::stage_roots(plan, d_x, fixed, st);
-        if (e != hipSuccess) return hip_fail(e, "root-plane launch");
+        if (!plan->direct) {
+            e = scratch_address(plan->device, &fixed);
+            if (e != hipSuccess) return hip_fail(e, "address of the fixed root-plane scratch");
+            // every element the kernel reads is written here first: nothing needs clearing
+            e = dmas::stage_roots(plan, d_x, fixed, st);
+            if (e != hipSuccess) return hip_fail(e, "root-plane launch");
+        }
         e = dmas::launch_image(plan, d_x, fixed, d_out, in_scale, env, st);
         if (e == hipErrorNotSupported)
             return fail(DMAS_ERR_UNSUPPORTED, "no kernel for order %d cf=%d env=%d near=%d accumulate=%d",
@@ -510,7 +527,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
         if (e != hipSuccess) return hip_fail(e, "kernel launch");
         return DMAS_OK;
     }
-    if (plan->roots) {
+    if (plan->roots && !plan->direct) {
         hipMemPool_t pool = nullptr;
         e = device_pool(plan->device, &pool);
         if (e != hipSuccess) return hip_fail(e, "root-plane memory pool");
@@ -689,10 +706,13 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     // global-to-LDS loads). With Kahan or FP64 sums, whose register budgets
     // differ, the per-microphone reads one ahead stay (1.4-2.4 % faster
     // there). DMAS_BLOCK_TABLES=0/1 overrides the choice for M <= 64 (tuning).
-    p->block_tables = M > dmas::kWaveSize || p->compensated == DMAS_ACCUM_F32;
+    p->direct = p->roots && p->tables && direct_roots_pay(p);
+    if (const char *dr = std::getenv("DMAS_DIRECT_ROOTS")) p->direct = p->roots && p->tables && std::atoi(dr) != 0;
+    p->block_tables = M > dmas::kWaveSize || p->compensated == DMAS_ACCUM_F32 || p->direct;
     if (const char *bt = std::getenv("DMAS_BLOCK_TABLES"))
         p->block_tables = M > dmas::kWaveSize || std::atoi(bt) != 0;
     p->block_tables = p->block_tables && p->tables;
+    p->direct = p->direct && p->block_tables && !std::getenv("DMAS_RING_SHARING");
     const int C = dmas::kChunk;
     const int H = (L - 1) / 2;
     p->row = C + 2 * p->halo + (p->linear ? 1 : 0);
@@ -791,6 +811,9 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         plan_free(p);
         return fail(DMAS_ERR_DEVICE, "internal: LDS layout mismatch");
     }
+
+    if (p->direct && std::max(dmas::direct_shape_of(p, true).lds_bytes, dmas::direct_shape_of(p, false).lds_bytes) > lds_cap)
+        p->direct = false;
 
     // Build the delay tables: the kernel reads window offsets and reference
     // delays instead of evaluating eq. (1) on the device and moving the

@@ -21,7 +21,8 @@ constexpr int kTableBlockMax = 16;  // the largest, for padding the tables
 struct KernelParams {
     const void *x;            // M x T channels (dtype below), device
     const float2 *roots;      // M x T (signed root, sample) pairs, device; used by
-                              // plans that stage roots (whole-sample delays, n >= 2)
+                              // plans that stage roots (whole-sample delays, n >= 2);
+                              // unused with kDelayTableDirect
     float *out;               // D x T image, device
     const double *mic;        // M x 3, device
     const double *dirs;       // D x 3, device
@@ -78,11 +79,17 @@ struct LaunchShape {
 // order 7.
 // kDelayTableBlocksShared is kDelayTableBlocks with the envelope rings in the
 // window region (below), which the plan picks when it raises the occupancy.
-enum : int { kDelayComputed = 0, kDelayLinear = 1, kDelayTable = 2, kDelayTableBlocks = 3, kDelayTableBlocksShared = 4 };
+// kDelayTableDirect is kDelayTableBlocks with the roots taken from the
+// channels while staging: single calls of small frames, n >= 2. A mode of its
+// own, because the staging code raised the other kernels' SGPRs past the
+// budget of eight waves per SIMD.
+enum : int { kDelayComputed = 0, kDelayLinear = 1, kDelayTable = 2, kDelayTableBlocks = 3, kDelayTableBlocksShared = 4,
+             kDelayTableDirect = 5 };
 __host__ __device__ constexpr bool block_tables(int delay)
 {
-    return delay == kDelayTableBlocks || delay == kDelayTableBlocksShared;
+    return delay == kDelayTableBlocks || delay == kDelayTableBlocksShared || delay == kDelayTableDirect;
 }
+__host__ __device__ constexpr bool takes_roots(int delay) { return delay == kDelayTableDirect; }
 
 // Compile-time tiling shared by host and device: waves (= directions) per
 // workgroup and output samples per lane per chunk.

@@ -266,6 +266,29 @@ __device__ __forceinline__ void stage_row_roots(float2 *__restrict__ dst, const 
     }
 }
 
+// The same window with the roots taken while staging, from the channels
+// themselves: for small frames, whose root pass and plane (allocated around
+// the call) take longer than the roots of every window.
+template <int N, int DT>
+__device__ __forceinline__ void stage_row_direct(float2 *__restrict__ dst, const void *__restrict__ x, size_t chan,
+                                                 int base, int row, int T, int lane)
+{
+    constexpr int U = 4;   // loads in flight per lane
+    for (int r0 = 0; r0 < row; r0 += U * kWaveSize) {
+        float v[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int r = r0 + kWaveSize * j + lane, t = base + r;
+            v[j] = (r < row && t >= 0 && t < T) ? load_sample<DT>(x, chan + (size_t)t) : 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int r = r0 + kWaveSize * j + lane;
+            if (r < row) dst[r] = make_float2(signed_root<N, true>(v[j]), v[j]);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Power-sum accumulators for one output sample.
 //   p[k], k = 1..N-1 : P_k = sum_i s_i^k                        eq. (7)
@@ -817,7 +840,10 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                     const int base = tc + dref_of(blk, i) - p.halo;
                     const size_t chan = (size_t)mic * (size_t)p.T;
                     if constexpr (ROOTS) {
-                        stage_row_roots(dst, p.roots, chan, base, p.row, p.T, lane);
+                        if constexpr (!takes_roots(DM)) stage_row_roots(dst, p.roots, chan, base, p.row, p.T, lane);
+                        else if (p.dtype == 0) stage_row_direct<N, 0>(dst, p.x, chan, base, p.row, p.T, lane);
+                        else if (p.dtype == 1) stage_row_direct<N, 1>(dst, p.x, chan, base, p.row, p.T, lane);
+                        else stage_row_direct<N, 2>(dst, p.x, chan, base, p.row, p.T, lane);
                     } else {
                         if (p.dtype == 0) stage_row<0>(dst, p.x, chan, base, p.row, p.T, lane);
                         else if (p.dtype == 1) stage_row<1>(dst, p.x, chan, base, p.row, p.T, lane);
@@ -1117,6 +1143,9 @@ hipError_t launch_order(const KernelParams *p, const LaunchShape &s, hipStream_t
     DMAS_WHOLE(kDelayTable)
     DMAS_WHOLE(kDelayTableBlocks)
     DMAS_WHOLE(kDelayTableBlocksShared)
+    if constexpr (N >= 2) {
+        DMAS_WHOLE(kDelayTableDirect)
+    }
     DMAS_WHOLE(kDelayComputed)
     DMAS_CASE(true, false, false, kDelayLinear, kAccF32)
     DMAS_CASE(true, true, false, kDelayLinear, kAccF32)

@@ -26,6 +26,7 @@ struct dmas_plan_s {
     int M = 0, T = 0, D = 0, order = 0;
     bool cf = true, nearfield = false, linear = false;
     bool roots = false;    // kernel reads a root plane (whole-sample delays, n >= 2)
+    bool direct = false;   // single calls take the roots while staging, without a root plane
     bool tables = false;   // per-tile delay tables (whole-sample delays, <= 2 GiB)
     bool block_tables = false;   // tables read a block of offsets at a time (kDelayTableBlocks)
     bool share_rings = false;    // with them, the envelope rings in the window region (...Shared)
@@ -124,6 +125,16 @@ inline LaunchShape shape_of(const dmas_plan_s *p, bool env)
     return ls;
 }
 
+// The launch of a plan with `direct` without a root plane (no rings in the
+// window region: that layout is for launches that fill the device).
+inline LaunchShape direct_shape_of(const dmas_plan_s *p, bool env)
+{
+    LaunchShape ls = shape_of(p, env);
+    ls.delay = kDelayTableDirect;
+    ls.lds_bytes = (size_t)kernel_lds_bytes(p->mic_block, p->row, 2, env, (p->fir_len - 1) / 2, kDelayTableDirect);
+    return ls;
+}
+
 // Workgroups of one launch of the plan.
 inline int64_t plan_workgroups(const dmas_plan_s *p, bool env)
 {
@@ -144,7 +155,8 @@ inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const f
 {
     const bool fused = env && !plan->two_pass;
     const KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused);
-    hipError_t e = launch_plan(plan->order, &kp, shape_of(plan, fused), stream);
+    hipError_t e = launch_plan(plan->order, &kp, plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused),
+                               stream);
     if (e == hipSuccess && env && !fused)
         e = launch_envelope_rows(d_out, plan->d_taps, plan->D, plan->T, plan->fir_len, plan->cus, stream);
     return e;

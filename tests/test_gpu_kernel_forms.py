@@ -54,3 +54,77 @@ def test_two_pass_envelope_in_an_unaligned_output(monkeypatch):
     np.testing.assert_array_equal(got, ref)
     rest = torch.cat([buf[:3], buf[3 + 10 * 2064:]]).cpu().numpy()
     assert (rest == 7.0).all()
+
+
+# (M, D, T, order): microphone blocks of one partial, one full, several; a record shorter than a
+# window; a window tail shorter than a wave
+DIRECT = [(3, 5, 40, 2), (8, 64, 1024, 2), (16, 9, 257, 3), (17, 30, 700, 4), (33, 21, 512, 5), (70, 12, 300, 8)]
+
+
+@pytest.mark.parametrize("M,D,T,n", DIRECT)
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("nearfield", [False, True])
+def test_roots_taken_while_staging_give_the_plane_bits(M, D, T, n, dtype, nearfield, monkeypatch):
+    """Small frames take the signed roots while staging; the image and envelope equal, bit for bit,
+    those of a plan that reads them from a root plane, and the plane-free call needs no scratch."""
+    from paper_2511_09165_amd import plan_for_frame
+    f = synth.random_frame(np.random.default_rng(M + D + T + n), M, D, T, n, nearfield=nearfield)
+    x = f.x_f32()
+    x[0, ::7] = 0.0
+    x[M // 2, 3::11] = np.float32(1e-39)                     # below the FP32 normal range
+    xt = torch.from_numpy(x).cuda().to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype])
+    _say(f"direct roots M={M} D={D} T={T} n={n} {dtype} near={nearfield}")
+    got = {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        with plan_for_frame(f, in_dtype=dtype) as plan:
+            env = torch.empty((D, T), dtype=torch.float32, device="cuda")
+            got[direct] = [plan.beamform(xt), plan.envelope(xt), plan.envelope_noalloc(xt, env)]
+            torch.cuda.synchronize()
+    for a, b in zip(got["0"], got["1"]):
+        assert torch.equal(a, b)
+    if dtype == "f32":
+        check_t1(got["1"][0].cpu().numpy(), oracle.frame_rows(f, x=x.astype(np.float64)))
+
+
+@pytest.mark.parametrize("accumulate", ["kahan", "f64"])
+@pytest.mark.parametrize("n", [2, 5, 7])
+def test_direct_roots_with_other_sums(accumulate, n, monkeypatch):
+    """The same for the compensated and FP64 sums, with more microphones than one table block."""
+    f = synth.random_frame(np.random.default_rng(9 + n), 21, 33, 900, n)
+    _say(f"direct roots {accumulate} n={n}")
+    got = {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        got[direct] = _image(f, f.x_f32(), accumulate=accumulate)
+    np.testing.assert_array_equal(got["0"], got["1"])
+    y_ref = oracle.frame_rows(f, x=f.x_f32().astype(np.float64))
+    taps = oracle.lowpass_taps(63, 5000.0, f.fs).astype(np.float32).astype(np.float64)
+    check_t1(got["1"], oracle.envelope(y_ref, taps))
+
+
+def test_direct_plan_in_a_graph_and_on_two_streams():
+    """A plan without a root plane replays from a graph, with eager calls between, and runs on two
+    streams at once: every result equals the eager one."""
+    from paper_2511_09165_amd import plan_for_frame
+    f = synth.random_frame(np.random.default_rng(5), 12, 40, 1500, 3)
+    _say("direct plan, graph and streams")
+    with plan_for_frame(f) as plan:
+        x = torch.from_numpy(f.x_f32()).cuda()
+        ref = plan.envelope(x)
+        out = torch.empty_like(ref)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            plan.envelope(x, out=out)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            plan.envelope(x, out=out)
+        for _ in range(3):
+            out.fill_(float("nan"))
+            g.replay()
+            with torch.cuda.stream(side):
+                other = plan.envelope(x)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref) and torch.equal(other, ref)
