@@ -260,6 +260,28 @@ void choose_rf_segments(int T, int num_tiles, int64_t slots, int fixed, int *seg
     *nseg = (T + s - 1) / s;
 }
 
+// Zero pairs around the rows of single calls' root planes, so that windows
+// reaching past the record's ends are copied like all others instead of
+// element by element, which took several times as long: workgroups at the ends
+// outlasted the rest (517 microphones, 361 x 4096 at order 2: 157 us against
+// 100 us each, and the launch lasted as long as they did). A delay is at most
+// the microphone's distance from the origin in samples (the triangle
+// inequality, near and far field); a window starts at most that and the halo
+// before sample 0 and ends at most that, a chunk and the halo after T. Rows
+// that would more than double (plus 1024 samples) stay unpadded.
+void plane_pads(const dmas_plan_desc_t *d, double c, int chunk, dmas_plan_s *p)
+{
+    double r2 = 0;
+    for (int i = 0; i < d->num_mics; ++i) {
+        const double *r = d->mic_pos + 3 * (size_t)i;
+        r2 = std::max(r2, r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+    }
+    const double reach = std::ceil(d->fs * std::sqrt(r2) / c * (1.0 + 1e-5)) + 2.0 + p->halo;
+    if (2.0 * reach + chunk + 4 > (double)p->T + 1024) return;
+    p->pad0 = ((int)reach + 3) & ~3;
+    p->pad1 = ((int)reach + chunk + 4 + 3) & ~3;
+}
+
 // Whether a single call takes the roots while staging instead of reading them
 // from a root plane (the same bits). The plane costs a launch (2-3 us) and a
 // pool allocation and free around the call (about 15 us of host time, which
@@ -513,14 +535,15 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
                         "dmas_envelope_noalloc",
                         need, plan->M, plan->T, (size_t)DMAS_NOALLOC_SCRATCH_BYTES);
         float2 *fixed = nullptr;
+        const bool padded = dmas::padded_plane_bytes(plan) <= DMAS_NOALLOC_SCRATCH_BYTES;
         if (!plan->direct) {
             e = scratch_address(plan->device, &fixed);
             if (e != hipSuccess) return hip_fail(e, "address of the fixed root-plane scratch");
             // every element the kernel reads is written here first: nothing needs clearing
-            e = dmas::stage_roots(plan, d_x, fixed, st);
+            e = dmas::stage_roots(plan, d_x, fixed, padded, st);
             if (e != hipSuccess) return hip_fail(e, "root-plane launch");
         }
-        e = dmas::launch_image(plan, d_x, fixed, d_out, in_scale, env, st);
+        e = dmas::launch_image(plan, d_x, fixed, padded, d_out, in_scale, env, st);
         if (e == hipErrorNotSupported)
             return fail(DMAS_ERR_UNSUPPORTED, "no kernel for order %d cf=%d env=%d near=%d accumulate=%d",
                         plan->order, (int)plan->cf, (int)env, (int)plan->nearfield, (int)plan->compensated);
@@ -531,15 +554,15 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
         hipMemPool_t pool = nullptr;
         e = device_pool(plan->device, &pool);
         if (e != hipSuccess) return hip_fail(e, "root-plane memory pool");
-        e = hipMallocFromPoolAsync(reinterpret_cast<void **>(&plane), dmas::plane_bytes(plan), pool, st);
+        e = hipMallocFromPoolAsync(reinterpret_cast<void **>(&plane), dmas::padded_plane_bytes(plan), pool, st);
         if (e != hipSuccess) return hip_fail(e, "root-plane allocation");
-        e = dmas::stage_roots(plan, d_x, plane, st);
+        e = dmas::stage_roots(plan, d_x, plane, true, st);
         if (e != hipSuccess) {
             (void)hipFreeAsync(plane, st);
             return hip_fail(e, "root-plane launch");
         }
     }
-    e = dmas::launch_image(plan, d_x, plane, d_out, in_scale, env, st);
+    e = dmas::launch_image(plan, d_x, plane, true, d_out, in_scale, env, st);
     if (plane) {
         const hipError_t ef = hipFreeAsync(plane, st);
         if (e == hipSuccess) e = ef;
@@ -815,6 +838,8 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     if (p->direct && std::max(dmas::direct_shape_of(p, true).lds_bytes, dmas::direct_shape_of(p, false).lds_bytes) > lds_cap)
         p->direct = false;
 
+    if (p->roots) plane_pads(d, c, C, p);
+
     // Build the delay tables: the kernel reads window offsets and reference
     // delays instead of evaluating eq. (1) on the device and moving the
     // results between lanes.
@@ -823,7 +848,8 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         // kTableBlockMax spare entries: a scalar block read may run past the last row
         e = hipMalloc((void **)&p->d_tile_off, sizeof(int32_t) * (n_off + dmas::kTableBlockMax));
         if (e == hipSuccess) e = hipMemset(p->d_tile_off + n_off, 0, sizeof(int32_t) * dmas::kTableBlockMax);
-        if (e == hipSuccess) e = hipMalloc((void **)&p->d_tile_dref, sizeof(int32_t) * n_dref);
+        if (e == hipSuccess) e = hipMalloc((void **)&p->d_tile_dref, sizeof(int32_t) * (n_dref + dmas::kTableBlockMax));
+        if (e == hipSuccess) e = hipMemset(p->d_tile_dref + n_dref, 0, sizeof(int32_t) * dmas::kTableBlockMax);
         if (e == hipSuccess) {
             auto kern = p->nearfield ? tile_table_kernel<true> : tile_table_kernel<false>;
             hipLaunchKernelGGL(kern, dim3(p->num_tiles), dim3(W * dmas::kWaveSize), 0, nullptr, p->d_mic, p->d_dirs,
@@ -840,7 +866,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
 
     p->device_bytes = sizeof(double) * 3 * ((size_t)M + (size_t)D) + sizeof(int32_t) * tiles.size() +
                       sizeof(float) * taps.size() + sizeof(float) * (size_t)p->mf_len +
-                      (p->d_tile_off ? sizeof(int32_t) * ((size_t)p->num_tiles * W * M + dmas::kTableBlockMax +
+                      (p->d_tile_off ? sizeof(int32_t) * ((size_t)p->num_tiles * W * M + 2 * dmas::kTableBlockMax +
                                                           (size_t)p->num_tiles * M)
                                      : 0);
 

@@ -20,9 +20,10 @@ constexpr int kTableBlockMax = 16;  // the largest, for padding the tables
 // Everything a beamforming launch needs, passed by value as the kernel argument.
 struct KernelParams {
     const void *x;            // M x T channels (dtype below), device
-    const float2 *roots;      // M x T (signed root, sample) pairs, device; used by
-                              // plans that stage roots (whole-sample delays, n >= 2);
-                              // unused with kDelayTableDirect
+    const float2 *roots;      // (signed root, sample) pairs, device: sample t of microphone
+                              // i at i * plane_stride + t, plane_lo <= t < plane_hi (zero
+                              // pairs outside [0, T)); used by plans that stage roots
+                              // (whole-sample delays, n >= 2), not with kDelayTableDirect
     float *out;               // D x T image, device
     const double *mic;        // M x 3, device
     const double *dirs;       // D x 3, device
@@ -46,6 +47,7 @@ struct KernelParams {
     float cf_eps;
     float in_scale;
     int32_t env_decim;        // envelope keeps every env_decim-th sample
+    int32_t plane_stride, plane_lo, plane_hi;   // layout of roots
     int32_t out_T;            // output row length: T, or ceil(T / env_decim) for the envelope
 };
 
@@ -173,9 +175,11 @@ hipError_t launch_batch_order6(const BatchParams &, bool, bool, bool, int, unsig
 hipError_t launch_batch_order7(const BatchParams &, bool, bool, bool, int, unsigned, size_t, hipStream_t);
 hipError_t launch_batch_order8(const BatchParams &, bool, bool, bool, int, unsigned, size_t, hipStream_t);
 
-// Root plane of a frame: plane[e] = (sgn(x_e) |x_e|^(1/order), x_e) for the
-// count = M * T channel samples of x (storage type dtype), in FP32.
-hipError_t launch_roots(int order, int dtype, const void *x, float2 *plane, size_t count, hipStream_t stream);
+// Root plane of a frame: M rows of pad0 + T + pad1 pairs, the pair of sample x
+// (storage type dtype) being (sgn(x) |x|^(1/order), x) in FP32, zero pairs in
+// the padding.
+hipError_t launch_roots(int order, int dtype, const void *x, float2 *plane, int M, int T, int pad0, int pad1,
+                        hipStream_t stream);
 
 // Envelope filter of an RF image (D rows of T samples) in place, for the plan's
 // taps on the device (L of them, zero-padded); cus: compute units of the device.

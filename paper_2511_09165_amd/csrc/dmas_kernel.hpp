@@ -159,6 +159,28 @@ __device__ __forceinline__ float to_f32(typename StorageOf<DT>::type v)
     else return __uint_as_float((uint32_t)v << 16);
 }
 
+// Copy `pieces` x 16 bytes from src (wave-uniform) to dst in LDS by
+// global-to-LDS loads. Whole KiB of a short row use immediate offsets, which
+// apply to both addresses, so they cost no vector instruction and one scalar
+// one each; the last, partial KiB is masked by lane.
+__device__ __forceinline__ void copy_row_to_lds(float *__restrict__ dst, const char *__restrict__ src, int pieces,
+                                                int lane)
+{
+    typedef __attribute__((address_space(3))) void lds_void;
+    unsigned at = (unsigned)lane * 16u;
+    asm("" : "+v"(at));   // kept 32 bits wide: a scalar base and a 32-bit lane offset per load
+    if (pieces >= 2 * kWaveSize) {
+        __builtin_amdgcn_global_load_lds(src + at, (lds_void *)dst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(src + at, (lds_void *)dst, 16, 1024, 0);
+        src += 2048;
+        dst += 512;
+        pieces -= 2 * kWaveSize;
+    }
+    for (; pieces >= kWaveSize; pieces -= kWaveSize, src += 1024, dst += 256)
+        __builtin_amdgcn_global_load_lds(src + at, (lds_void *)dst, 16, 0, 0);
+    if (lane < pieces) __builtin_amdgcn_global_load_lds(src + at, (lds_void *)dst, 16, 0, 0);
+}
+
 // One microphone's window [base, base + row) of the channel starting at
 // element chan, converted to FP32, zero outside [0, T); used where samples
 // rather than roots are staged (n = 1, linear delays). Windows inside the
@@ -173,14 +195,8 @@ __device__ __forceinline__ void stage_row(float *__restrict__ dst, const void *_
 {
     using E = typename StorageOf<DT>::type;
     if (DT == 0 && base >= 0 && base + row <= T) {
-        typedef __attribute__((address_space(3))) void lds_void;
-        const char *src = reinterpret_cast<const char *>(static_cast<const float *>(x) + chan + (size_t)base);
-        const int pieces = row >> 2;
-        for (int q = 0; q < pieces; q += kWaveSize) {
-            if (lane < pieces - q)
-                __builtin_amdgcn_global_load_lds(src + (unsigned)(q + lane) * 16u, (lds_void *)(dst + 4 * q), 16, 0,
-                                                 0);
-        }
+        copy_row_to_lds(dst, reinterpret_cast<const char *>(static_cast<const float *>(x) + chan + (size_t)base),
+                        row >> 2, lane);
     } else if (base >= 0 && base + row <= T) {
         const E *src = static_cast<const E *>(x) + chan + (size_t)base + lane;
         float *d = dst + lane;
@@ -224,44 +240,59 @@ __device__ __forceinline__ float signed_root(float xv)
 template <int N, bool LINEAR>
 constexpr bool kStagesRoots = N >= 2 && !LINEAR;
 
-// Root plane: plane[e] = (signed_root(x_e), x_e) over count samples.
+// Root plane: row i holds (signed_root(x), x) of channel i's samples at
+// [pad0, pad0 + T) and zero pairs elsewhere in its `stride` elements. A
+// workgroup takes kRootBlock elements of one row.
+constexpr int kRootThreads = 256;
+constexpr int kRootBlock = 4 * kRootThreads;
 template <int N, int DT>
-__global__ void __launch_bounds__(256) root_plane_kernel(const void *__restrict__ x, float2 *__restrict__ plane,
-                                                         size_t count)
+__global__ void __launch_bounds__(kRootThreads)
+root_plane_kernel(const void *__restrict__ x, float2 *__restrict__ plane, int T, int pad0, int stride, int blocks)
 {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride) {
-        const float v = load_sample<DT>(x, e);
-        plane[e] = make_float2(signed_root<N, true>(v), v);
+    const int mic = blockIdx.x / blocks;
+    const int e0 = (blockIdx.x - mic * blocks) * kRootBlock + threadIdx.x;
+    const size_t chan = (size_t)mic * (size_t)T, row = (size_t)mic * (size_t)stride;
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int t = e0 + j * kRootThreads - pad0;
+        v[j] = t >= 0 && t < T ? load_sample<DT>(x, chan + (size_t)t) : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int e = e0 + j * kRootThreads;
+        if (e < stride) plane[row + (size_t)e] = make_float2(signed_root<N, true>(v[j]), v[j]);
     }
 }
 
-// One microphone's window [base, base + row) of the root plane starting at
-// element chan, (0, 0) outside [0, T) (the pair of a zero sample). A window
-// inside the record (all but the first and last chunks) is copied by the
-// global-to-LDS loads: each lane moves 16 bytes (two pairs) straight into LDS
-// at M0 + 16 * lane, a wave 1 KiB per load, with no vector registers and no
-// vector ALU work; row is a multiple of 4 pairs, so the copy is whole 16-byte
-// pieces into 32-byte aligned LDS rows. Those copies complete in the
-// background (the wave's vmcnt): the caller waits for them before the barrier
-// that publishes the windows. (Against loading into registers and writing
-// them to LDS: 4.0-7.5 % faster across the kernels, bitwise the same.)
-__device__ __forceinline__ void stage_row_roots(float2 *__restrict__ dst, const float2 *__restrict__ plane,
-                                                size_t chan, int base, int row, int T, int lane)
+// One microphone's window [base, base + row) of its row of the root plane
+// (plane: the row's sample 0), (0, 0) outside [0, T) (the pair of a zero
+// sample). The row holds the pairs of [lo, hi), zeros outside [0, T); a window
+// inside it is copied by global-to-LDS loads, which complete in the background
+// (the wave's vmcnt): the caller waits for them before the barrier that
+// publishes the windows. Planes of single calls are padded so that every
+// window is (plane_pads). (Against loading into registers and writing those to
+// LDS: 4.0-7.5 % faster across the kernels, bitwise the same.)
+__device__ __forceinline__ void stage_row_roots(float2 *__restrict__ dst, const float2 *__restrict__ plane, int base,
+                                                int row, int lo, int hi, int T, int lane)
 {
-    if (base >= 0 && base + row <= T) {
-        typedef __attribute__((address_space(3))) void lds_void;
-        const char *src = reinterpret_cast<const char *>(plane + chan + (size_t)base);
-        const int pieces = row >> 1;
-        for (int q = 0; q < pieces; q += kWaveSize) {   // wave-uniform
-            if (lane < pieces - q)
-                __builtin_amdgcn_global_load_lds(src + (unsigned)(q + lane) * 16u, (lds_void *)(dst + 2 * q), 16, 0,
-                                                 0);
-        }
+    if (base >= lo && base + row <= hi) {
+        copy_row_to_lds(reinterpret_cast<float *>(dst), reinterpret_cast<const char *>(plane + (ptrdiff_t)base),
+                        row >> 1, lane);
     } else {
-        for (int r = lane; r < row; r += kWaveSize) {
-            const int t = base + r;
-            dst[r] = (t >= 0 && t < T) ? plane[chan + (size_t)t] : make_float2(0.0f, 0.0f);
+        constexpr int U = 4;   // loads in flight per lane
+        for (int r0 = 0; r0 < row; r0 += U * kWaveSize) {
+            float2 v[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int r = r0 + kWaveSize * j + lane, t = base + r;
+                v[j] = (r < row && t >= 0 && t < T) ? plane[t] : make_float2(0.0f, 0.0f);
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int r = r0 + kWaveSize * j + lane;
+                if (r < row) dst[r] = v[j];
+            }
         }
     }
 }
@@ -529,6 +560,15 @@ __device__ __forceinline__ float fp32_out_scale(const KernelParams &p)
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
 
+// Barrier for LDS traffic alone: global stores in flight (the previous chunk's
+// outputs) are not waited for.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---------------------------------------------------------------------------
 // The kernel.
 // ---------------------------------------------------------------------------
@@ -607,8 +647,10 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
     //    do not change while a kernel runs), so the per-microphone LDS
     //    address of the hot loop costs one vector add. Either the hot loop
     //    reads each offset one microphone ahead (TAB), or (TAB_BLOCKS) a wave
-    //    reads its block's offsets as one scalar block before the block's
-    //    barrier, and the reference delays of the rows it stages;
+    //    reads its block's offsets as one scalar block, and the reference
+    //    delays of the rows it stages next, while the block's window copies
+    //    are under way (reading them before the copies put their latency in
+    //    front of every block: 1-5 % slower on the frames that stage most);
     //  * M <= 64 without tables (linear delays): lane i of every wave computes
     //    its direction's delay for microphone i once, and wave 0 (the tile's
     //    reference direction) publishes its delays in LDS for the staging step;
@@ -650,16 +692,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
     auto block_geometry = [&](int blk) {
         if (table) return;
         const int mic = blk * p.mic_block + lane;
-        if constexpr (TAB_BLOCKS) {
-            // scalar loads issued before the block's barrier so they overlap the wait
-            const_i32 *ob = off_srow + blk * p.mic_block;
-#pragma unroll
-            for (int k = 0; k < LB; ++k) soff[k] = ob[k];
-            const int r0 = blk * p.mic_block + wave;
-            sdref0 = (wave < p.mic_block && r0 < p.M) ? dref_row[r0] : 0;
-            sdref1 = (wave + W < p.mic_block && r0 + W < p.M) ? dref_row[r0 + W] : 0;
-            return;
-        }
+        if constexpr (TAB_BLOCKS) return;
         // the first block of a group computes the group's delays
         if (group_pos(blk) != 0) return;
         const int nlanes = all_mics ? p.M : p.mic_block << group_shift;
@@ -671,6 +704,18 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                 dref_lds[lane] = 0;
             }
         }
+    };
+    // Per-block tables: the reference delays of the rows this wave stages in
+    // block blk (the table is padded past its last row), and the block's offsets.
+    auto load_drefs = [&](int blk) {
+        const int r0 = blk * p.mic_block + wave;
+        sdref0 = dref_row[r0];
+        sdref1 = dref_row[r0 + W];
+    };
+    auto load_offsets = [&](int blk) {
+        const_i32 *ob = off_srow + blk * p.mic_block;
+#pragma unroll
+        for (int k = 0; k < LB; ++k) soff[k] = ob[k];
     };
     // Reference delay of microphone i (wave-uniform) of block blk, for staging.
     auto dref_of = [&](int blk, int i) {
@@ -805,6 +850,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
     };
 
     const float out_scale = fp32_out_scale<N>(p);
+    if constexpr (TAB_BLOCKS) load_drefs(0);
 
     // Power sums. Plain FP32 sums (PEEL): each chunk's first microphone starts
     // them, so they are the pass's own (nothing carried from one pass to the
@@ -827,7 +873,9 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
 
         for (int blk = 0; blk < (compute ? nblocks : 0); ++blk) {
             if (!all_mics) block_geometry(blk);
-            __syncthreads();  // reference delays visible; previous block's reads done
+            // reference delays visible; previous block's reads done
+            if constexpr (TAB_BLOCKS) lds_barrier();
+            else __syncthreads();
             block_offsets(blk);
             // ---- stage this block's channel windows into LDS ----
             // (issued at normal wave priority: raising it helped the loads
@@ -840,7 +888,9 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                     const int base = tc + dref_of(blk, i) - p.halo;
                     const size_t chan = (size_t)mic * (size_t)p.T;
                     if constexpr (ROOTS) {
-                        if constexpr (!takes_roots(DM)) stage_row_roots(dst, p.roots, chan, base, p.row, p.T, lane);
+                        if constexpr (!takes_roots(DM))
+                            stage_row_roots(dst, p.roots + (size_t)mic * (size_t)p.plane_stride, base, p.row, p.plane_lo,
+                                            p.plane_hi, p.T, lane);
                         else if (p.dtype == 0) stage_row_direct<N, 0>(dst, p.x, chan, base, p.row, p.T, lane);
                         else if (p.dtype == 1) stage_row_direct<N, 1>(dst, p.x, chan, base, p.row, p.T, lane);
                         else stage_row_direct<N, 2>(dst, p.x, chan, base, p.row, p.T, lane);
@@ -849,14 +899,25 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                         else if (p.dtype == 1) stage_row<1>(dst, p.x, chan, base, p.row, p.T, lane);
                         else stage_row<2>(dst, p.x, chan, base, p.row, p.T, lane);
                     }
-                } else {
-                    for (int r = lane; r < p.row; r += kWaveSize) dst[r] = Elem{};
-                }
+                }   // (rows past the last microphone are not read)
+            }
+            // per-block tables: the block's offsets and the next block's reference
+            // delays arrive under the copies
+            if constexpr (TAB_BLOCKS) {
+                load_offsets(blk);
+                load_drefs(blk + 1 < nblocks ? blk + 1 : 0);
             }
             // this wave's global-to-LDS copies have landed (vmcnt(0), the other
             // counters untouched; FP16/BF16 samples are staged through registers)
             if (ROOTS || p.dtype == 0) __builtin_amdgcn_s_waitcnt(0x0F70);
-            __syncthreads();
+            if constexpr (TAB_BLOCKS) {
+                // (read before the barrier: the compiler would move the loads behind it)
+#pragma unroll
+                for (int k = 0; k < LB; ++k) asm volatile("" : "+s"(soff[k]));
+                asm volatile("" : "+s"(sdref0), "+s"(sdref1));
+                lds_barrier();
+            }
+            else __syncthreads();
             // ---- hot loop: delayed samples -> roots -> power sums ----
             if (active) {
                 const int nm = min(p.mic_block, p.M - blk * p.mic_block);
@@ -919,9 +980,21 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                 } else if constexpr (TAB_BLOCKS) {
                     if (PEEL && blk == 0) mic_step(first_t{}, 0, soff[0]);
                     else mic_step(rest_t{}, 0, soff[0]);
+                    // a full block without a test per microphone, each one's reads
+                    // kept behind the sums before (grouped reads ran 3-10 % slower):
+                    // 0.4-3 % on RF kernels of orders up to 3; with the envelope or
+                    // at higher orders it raised the registers (order 5 8 % slower)
+                    if (N <= 3 && !ENV && ACC == kAccF32 && nm == LB) {
 #pragma unroll
-                    for (int i = 1; i < LB; ++i)
-                        if (i < nm) mic_step(rest_t{}, i, soff[i]);
+                        for (int i = 1; i < LB; ++i) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            mic_step(rest_t{}, i, soff[i]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int i = 1; i < LB; ++i)
+                            if (i < nm) mic_step(rest_t{}, i, soff[i]);
+                    }
                 } else {
                     const int g0 = group_lane(blk);
                     auto off_of = [&](int i) { return __builtin_amdgcn_readlane(myoff, g0 + i); };

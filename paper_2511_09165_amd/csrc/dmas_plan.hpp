@@ -26,6 +26,7 @@ struct dmas_plan_s {
     int M = 0, T = 0, D = 0, order = 0;
     bool cf = true, nearfield = false, linear = false;
     bool roots = false;    // kernel reads a root plane (whole-sample delays, n >= 2)
+    int pad0 = 0, pad1 = 0;   // zero pairs before and after a row of single calls' root planes
     bool direct = false;   // single calls take the roots while staging, without a root plane
     bool tables = false;   // per-tile delay tables (whole-sample delays, <= 2 GiB)
     bool block_tables = false;   // tables read a block of offsets at a time (kDelayTableBlocks)
@@ -65,20 +66,32 @@ inline size_t plane_bytes(const dmas_plan_s *plan)
     return plan->roots ? (size_t)plan->M * (size_t)plan->T * sizeof(float2) : 0;
 }
 
-// Fill the root plane of input d_x (plans with roots only).
-inline hipError_t stage_roots(const dmas_plan_s *plan, const void *d_x, float2 *d_plane, hipStream_t stream)
+// The same with the rows padded.
+inline size_t padded_plane_bytes(const dmas_plan_s *plan)
 {
-    return launch_roots(plan->order, plan->dtype, d_x, d_plane, (size_t)plan->M * (size_t)plan->T, stream);
+    return plan->roots ? (size_t)plan->M * ((size_t)plan->pad0 + (size_t)plan->T + (size_t)plan->pad1) * sizeof(float2)
+                       : 0;
+}
+
+// Fill the root plane of input d_x (plans with roots only).
+inline hipError_t stage_roots(const dmas_plan_s *plan, const void *d_x, float2 *d_plane, bool padded,
+                              hipStream_t stream)
+{
+    return launch_roots(plan->order, plan->dtype, d_x, d_plane, plan->M, plan->T, padded ? plan->pad0 : 0,
+                        padded ? plan->pad1 : 0, stream);
 }
 
 // Kernel arguments for one launch of `plan` on input d_x (and its root plane
 // d_plane when the plan uses one) / output d_out.
 inline KernelParams make_params(const dmas_plan_s *plan, const void *d_x, const float2 *d_plane, float *d_out,
-                                float in_scale, bool env)
+                                float in_scale, bool env, bool padded = false)
 {
     KernelParams kp{};
     kp.x = d_x;
-    kp.roots = d_plane;
+    kp.roots = d_plane && padded ? d_plane + plan->pad0 : d_plane;
+    kp.plane_lo = padded ? -plan->pad0 : 0;
+    kp.plane_hi = plan->T + (padded ? plan->pad1 : 0);
+    kp.plane_stride = kp.plane_hi - kp.plane_lo;
     kp.out = d_out;
     kp.mic = plan->d_mic;
     kp.dirs = plan->d_dirs;
@@ -150,11 +163,11 @@ hipError_t launch_plan(int order, const KernelParams *kp, const LaunchShape &ls,
 
 // Launch the beamformer of one call and, for an envelope in two passes, the
 // filter over its image (d_plane filled before, in stream order).
-inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const float2 *d_plane, float *d_out,
-                               float in_scale, bool env, hipStream_t stream)
+inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const float2 *d_plane, bool padded,
+                               float *d_out, float in_scale, bool env, hipStream_t stream)
 {
     const bool fused = env && !plan->two_pass;
-    const KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused);
+    const KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused, padded);
     hipError_t e = launch_plan(plan->order, &kp, plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused),
                                stream);
     if (e == hipSuccess && env && !fused)

@@ -7,30 +7,30 @@ namespace dmas {
 namespace {
 
 template <int N>
-hipError_t launch_roots_n(int dtype, const void *x, float2 *plane, size_t count, hipStream_t stream)
+hipError_t launch_roots_n(int dtype, const void *x, float2 *plane, int M, int T, int pad0, int pad1,
+                          hipStream_t stream)
 {
-    constexpr unsigned kThreads = 256;
-    const size_t want = (count + kThreads - 1) / kThreads;
-    const unsigned grid = (unsigned)(want < 8192 ? (want > 0 ? want : 1) : 8192);
-    if (dtype == 0) hipLaunchKernelGGL((root_plane_kernel<N, 0>), dim3(grid), dim3(kThreads), 0, stream, x, plane, count);
-    else if (dtype == 1) hipLaunchKernelGGL((root_plane_kernel<N, 1>), dim3(grid), dim3(kThreads), 0, stream, x, plane, count);
-    else hipLaunchKernelGGL((root_plane_kernel<N, 2>), dim3(grid), dim3(kThreads), 0, stream, x, plane, count);
+    const int stride = pad0 + T + pad1;
+    const int blocks = (stride + kRootBlock - 1) / kRootBlock;
+    const dim3 grid((unsigned)M * (unsigned)blocks), threads(kRootThreads);
+    auto kern = dtype == 0 ? root_plane_kernel<N, 0> : dtype == 1 ? root_plane_kernel<N, 1> : root_plane_kernel<N, 2>;
+    hipLaunchKernelGGL(kern, grid, threads, 0, stream, x, plane, T, pad0, stride, blocks);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_roots(int order, int dtype, const void *x, float2 *plane, size_t count, hipStream_t stream)
+hipError_t launch_roots(int order, int dtype, const void *x, float2 *plane, int M, int T, int pad0, int pad1,
+                        hipStream_t stream)
 {
-    if (count == 0) return hipSuccess;
     switch (order) {
-    case 2: return launch_roots_n<2>(dtype, x, plane, count, stream);
-    case 3: return launch_roots_n<3>(dtype, x, plane, count, stream);
-    case 4: return launch_roots_n<4>(dtype, x, plane, count, stream);
-    case 5: return launch_roots_n<5>(dtype, x, plane, count, stream);
-    case 6: return launch_roots_n<6>(dtype, x, plane, count, stream);
-    case 7: return launch_roots_n<7>(dtype, x, plane, count, stream);
-    case 8: return launch_roots_n<8>(dtype, x, plane, count, stream);
+    case 2: return launch_roots_n<2>(dtype, x, plane, M, T, pad0, pad1, stream);
+    case 3: return launch_roots_n<3>(dtype, x, plane, M, T, pad0, pad1, stream);
+    case 4: return launch_roots_n<4>(dtype, x, plane, M, T, pad0, pad1, stream);
+    case 5: return launch_roots_n<5>(dtype, x, plane, M, T, pad0, pad1, stream);
+    case 6: return launch_roots_n<6>(dtype, x, plane, M, T, pad0, pad1, stream);
+    case 7: return launch_roots_n<7>(dtype, x, plane, M, T, pad0, pad1, stream);
+    case 8: return launch_roots_n<8>(dtype, x, plane, M, T, pad0, pad1, stream);
     default: return hipErrorNotSupported;
     }
 }

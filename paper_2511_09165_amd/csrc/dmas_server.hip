@@ -388,7 +388,7 @@ struct dmas_server_s {
             // input copy, then the root plane, on the copy stream
             hipError_t e = hipMemcpyAsync(d_arena + f->in_off, h_staging + f->stage_off, f->in_bytes,
                                           hipMemcpyHostToDevice, copy_stream);
-            if (e == hipSuccess && f->plane_bytes) e = dmas::stage_roots(f->plan, d_arena + f->in_off, plane_of(f), copy_stream);
+            if (e == hipSuccess && f->plane_bytes) e = dmas::stage_roots(f->plan, d_arena + f->in_off, plane_of(f), false, copy_stream);
             if (e == hipSuccess && f->copied) e = hipEventRecord(f->copied, copy_stream);
             if (e != hipSuccess || !f->copied) {
                 (void)hipStreamSynchronize(copy_stream);   // done with the staging and arena ranges

@@ -128,3 +128,33 @@ def test_direct_plan_in_a_graph_and_on_two_streams():
                 other = plan.envelope(x)
             torch.cuda.synchronize()
             assert torch.equal(out, ref) and torch.equal(other, ref)
+
+
+def test_plane_rows_too_short_for_padding(monkeypatch):
+    """A wide array on a short record keeps its root plane unpadded; windows that reach past the
+    record then take the element-wise path: the same bits as roots taken while staging, and T1."""
+    f = synth.random_frame(np.random.default_rng(15), 9, 20, 300, 3)
+    f.mic_pos = f.mic_pos * (1.5 / np.abs(f.mic_pos).max())          # delays up to about 2000 samples
+    _say("unpadded plane")
+    got = {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        got[direct] = _image(f, f.x_f32())
+    np.testing.assert_array_equal(got["0"], got["1"])
+    taps = oracle.lowpass_taps(63, 5000.0, f.fs).astype(np.float32).astype(np.float64)
+    check_t1(got["0"], oracle.envelope(oracle.frame_rows(f, x=f.x_f32().astype(np.float64)), taps))
+
+
+def test_fixed_scratch_that_holds_only_the_unpadded_plane(monkeypatch):
+    """dmas_envelope_noalloc at its limit: the plane fills the fixed scratch without padding, and
+    gives the bits of the padded plane from the pool."""
+    from paper_2511_09165_amd import plan_for_frame
+    monkeypatch.setenv("DMAS_DIRECT_ROOTS", "0")
+    f = synth.random_frame(np.random.default_rng(16), 64, 9, 32768, 2)
+    _say("plane of exactly the fixed scratch")
+    with plan_for_frame(f) as plan:
+        x = torch.from_numpy(f.x_f32()).cuda()
+        ref = plan.envelope(x)
+        out = plan.envelope_noalloc(x, torch.empty_like(ref))
+        torch.cuda.synchronize()
+        assert torch.equal(ref, out)
