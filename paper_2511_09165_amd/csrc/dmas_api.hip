@@ -65,64 +65,81 @@ uint32_t spread_bits(uint32_t v)
 
 namespace {
 
-// Per-tile maximum |whole delay - reference whole delay| over all microphones.
+// Smallest and largest whole delay of microphone i over a tile's directions,
+// and that of its first (reference) direction.
 template <bool NEAR, bool LINEAR>
-__global__ void __launch_bounds__(dmas::kDirsPerTile * dmas::kWaveSize)
-tile_spread_kernel(const double *__restrict__ mic, const double *__restrict__ dirs,
-                   const int32_t *__restrict__ tiles, int M, double fs, double c,
-                   int32_t *__restrict__ out)
+__device__ __forceinline__ void tile_delays(const double *mic, const double *__restrict__ dirs,
+                                            const int32_t *__restrict__ tile, double fs, double c, int *ref, int *lo,
+                                            int *hi)
 {
-    constexpr int W = dmas::kDirsPerTile;
-    __shared__ int wave_max[W];
-    const int lane = threadIdx.x % dmas::kWaveSize;
-    const int wave = threadIdx.x / dmas::kWaveSize;
-    const int dir = tiles[blockIdx.x * W + wave];
-    const int dir0 = tiles[blockIdx.x * W];
-    int m = 0;
-    if (dir >= 0) {
-        for (int i = lane; i < M; i += dmas::kWaveSize) {
-            float f;
-            const int d0 = dmas::steer_whole<NEAR, LINEAR>(mic + 3 * i, dirs + 3 * dir0, fs, c, &f);
-            const int dw = dmas::steer_whole<NEAR, LINEAR>(mic + 3 * i, dirs + 3 * dir, fs, c, &f);
-            m = max(m, abs(dw - d0));
-        }
-    }
-    for (int s = dmas::kWaveSize / 2; s > 0; s >>= 1) m = max(m, __shfl_xor(m, s));
-    if (lane == 0) wave_max[wave] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int r = 0;
-        for (int w = 0; w < W; ++w) r = max(r, wave_max[w]);
-        out[blockIdx.x] = r;
+    float f;
+    const int d0 = dmas::steer_whole<NEAR, LINEAR>(mic, dirs + 3 * tile[0], fs, c, &f);
+    *ref = *lo = *hi = d0;
+    for (int w = 1; w < dmas::kDirsPerTile; ++w) {
+        if (tile[w] < 0) continue;
+        const int d = dmas::steer_whole<NEAR, LINEAR>(mic, dirs + 3 * tile[w], fs, c, &f);
+        *lo = min(*lo, d);
+        *hi = max(*hi, d);
     }
 }
 
-// Per-tile delay tables: the reference delays (the tile's first direction)
-// and, per direction and microphone, the LDS element where the kernel finds
-// that direction's window: (mic % mic_block) * row + clamp(delay - reference
-// + halo, 0, 2 halo); empty direction slots get the row start.
+// Per tile, over all microphones: the maximum |whole delay - reference whole
+// delay| and the maximum range of a microphone's whole delays.
+template <bool NEAR, bool LINEAR>
+__global__ void __launch_bounds__(dmas::kDirsPerTile * dmas::kWaveSize)
+tile_spread_kernel(const double *__restrict__ mic, const double *__restrict__ dirs,
+                   const int32_t *__restrict__ tiles, int M, double fs, double c, int2 *__restrict__ out)
+{
+    constexpr int W = dmas::kDirsPerTile;
+    __shared__ int2 wave_max[W];
+    const int lane = threadIdx.x % dmas::kWaveSize;
+    const int wave = threadIdx.x / dmas::kWaveSize;
+    int halo = 0, range = 0;
+    for (int i = threadIdx.x; i < M; i += W * dmas::kWaveSize) {
+        int ref, lo, hi;
+        tile_delays<NEAR, LINEAR>(mic + 3 * i, dirs, tiles + blockIdx.x * W, fs, c, &ref, &lo, &hi);
+        halo = max(halo, max(hi - ref, ref - lo));
+        range = max(range, hi - lo);
+    }
+    for (int s = dmas::kWaveSize / 2; s > 0; s >>= 1) {
+        halo = max(halo, __shfl_xor(halo, s));
+        range = max(range, __shfl_xor(range, s));
+    }
+    if (lane == 0) wave_max[wave] = make_int2(halo, range);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < W; ++w) {
+            halo = max(halo, wave_max[w].x);
+            range = max(range, wave_max[w].y);
+        }
+        out[blockIdx.x] = make_int2(halo, range);
+    }
+}
+
+// Per-tile delay tables: per microphone the delay its window starts at (the
+// smallest of the tile's directions), and per direction and microphone the LDS
+// element where the kernel finds that direction's window: (mic % mic_block) *
+// row + clamp(delay - start, 0, range); empty direction slots get the row
+// start.
 template <bool NEAR>
 __global__ void __launch_bounds__(dmas::kDirsPerTile * dmas::kWaveSize)
 tile_table_kernel(const double *__restrict__ mic, const double *__restrict__ dirs,
-                  const int32_t *__restrict__ tiles, int M, double fs, double c, int halo, int mic_block,
+                  const int32_t *__restrict__ tiles, int M, double fs, double c, int range, int mic_block,
                   int row, int32_t *__restrict__ off, int32_t *__restrict__ dref)
 {
     constexpr int W = dmas::kDirsPerTile;
-    const int lane = threadIdx.x % dmas::kWaveSize;
-    const int wave = threadIdx.x / dmas::kWaveSize;
-    const int dir = tiles[blockIdx.x * W + wave];
-    const int dir0 = tiles[blockIdx.x * W];
-    int32_t *dst = off + ((size_t)blockIdx.x * W + wave) * M;
-    for (int i = lane; i < M; i += dmas::kWaveSize) {
-        float f;
-        const int d0 = dmas::steer_whole<NEAR, false>(mic + 3 * i, dirs + 3 * dir0, fs, c, &f);
-        if (wave == 0) dref[(size_t)blockIdx.x * M + i] = d0;
-        int r = 0;
-        if (dir >= 0) {
-            const int dw = dmas::steer_whole<NEAR, false>(mic + 3 * i, dirs + 3 * dir, fs, c, &f);
-            r = min(max(dw - d0 + halo, 0), 2 * halo);
+    const int32_t *tile = tiles + blockIdx.x * W;
+    for (int i = threadIdx.x; i < M; i += W * dmas::kWaveSize) {
+        int ref, lo, hi;
+        tile_delays<NEAR, false>(mic + 3 * i, dirs, tile, fs, c, &ref, &lo, &hi);
+        dref[(size_t)blockIdx.x * M + i] = lo;
+        for (int w = 0; w < W; ++w) {
+            float f;
+            int r = 0;
+            if (tile[w] >= 0)
+                r = min(max(dmas::steer_whole<NEAR, false>(mic + 3 * i, dirs + 3 * tile[w], fs, c, &f) - lo, 0), range);
+            off[((size_t)blockIdx.x * W + w) * M + i] = (i % mic_block) * row + r;
         }
-        dst[i] = (i % mic_block) * row + r;
     }
 }
 
@@ -692,8 +709,8 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
 
     // ---- delay spread per tile, measured with the kernels' own delay code ----
     {
-        int32_t *d_spread = nullptr;
-        e = hipMalloc(&d_spread, sizeof(int32_t) * p->num_tiles);
+        int2 *d_spread = nullptr;
+        e = hipMalloc(&d_spread, sizeof(int2) * p->num_tiles);
         if (e != hipSuccess) {
             plan_free(p);
             return hip_fail(e, "spread buffer");
@@ -703,16 +720,19 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         hipLaunchKernelGGL(kern, dim3(p->num_tiles), dim3(W * dmas::kWaveSize), 0, nullptr, p->d_mic, p->d_dirs,
                            p->d_tiles, M, p->fs, p->c, d_spread);
         e = hipGetLastError();
-        std::vector<int32_t> spread(p->num_tiles);
+        std::vector<int2> spread(p->num_tiles);
         if (e == hipSuccess)
-            e = hipMemcpy(spread.data(), d_spread, sizeof(int32_t) * p->num_tiles, hipMemcpyDeviceToHost);
+            e = hipMemcpy(spread.data(), d_spread, sizeof(int2) * p->num_tiles, hipMemcpyDeviceToHost);
         (void)hipFree(d_spread);
         if (e != hipSuccess) {
             plan_free(p);
             return hip_fail(e, "tile spread");
         }
-        p->halo = 0;
-        for (int v : spread) p->halo = std::max(p->halo, v);
+        p->halo = p->range = 0;
+        for (const int2 &v : spread) {
+            p->halo = std::max(p->halo, v.x);
+            p->range = std::max(p->range, v.y);
+        }
     }
     // ---- LDS layout: mic_block x row windows, reference delays, envelope rings ----
     // Per-tile delay tables for whole-sample delays, when of modest size (the
@@ -738,8 +758,13 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     p->direct = p->direct && p->block_tables && !std::getenv("DMAS_RING_SHARING");
     const int C = dmas::kChunk;
     const int H = (L - 1) / 2;
-    p->row = C + 2 * p->halo + (p->linear ? 1 : 0);
-    p->row = (p->row + 3) & ~3;
+    // Window length. With tables a microphone's window starts at the smallest
+    // delay of the tile's directions; where the kernel evaluates the delays it
+    // knows only the reference direction's and allows the halo either side.
+    // (32 microphones, 4186 directions: rows of 288 instead of 296, 1.2 % faster
+    // at order 5; 64 microphones, 1035 directions: 336 instead of 380, 0.6 %.)
+    const int halo_row = (C + 2 * p->halo + (p->linear ? 1 : 0) + 3) & ~3;
+    p->row = p->tables ? (C + p->range + 3) & ~3 : halo_row;
     const size_t lds_cap = (size_t)prop.sharedMemPerBlock;
     // reference delays in LDS (kernels that evaluate delays on the device)
     const size_t fixed = sizeof(int) * dmas::dref_lds_ints(dmas::shape_of(p, true).delay);
@@ -756,6 +781,20 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
                                                      W * (share ? dmas::carry_stride(H) : dmas::ring_stride(H)));
         return fixed + (env ? (share ? std::max(win, ring_bytes) : win) + side : win);
     };
+    // (a plan whose window would not fit with the halo on both sides is refused
+    // with tables too, whose rows are shorter)
+    {
+        const size_t side = sizeof(float) * (size_t)(dmas::env_taps_len(H) + W * dmas::ring_stride(H));
+        const size_t carried = sizeof(float) * (size_t)(dmas::env_taps_len(H) + W * dmas::carry_stride(H));
+        const size_t win = elem * (size_t)halo_row;
+        const bool fits = fixed + win + side <= lds_cap ||
+                          (p->block_tables && fixed + std::max(win, ring_bytes) + carried <= lds_cap);
+        if (!fits) {
+            plan_free(p);
+            return fail(DMAS_ERR_UNSUPPORTED,
+                        "direction tiles spread over %d samples: the channel window does not fit in LDS", p->halo);
+        }
+    }
     // With per-block tables the kernel reads a block's offsets as one scalar
     // block of table_block_max(n) entries: that caps the block.
     const int mb_cap = p->block_tables ? dmas::table_block_max(n) : dmas::kMaxMicBlock;
@@ -853,7 +892,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         if (e == hipSuccess) {
             auto kern = p->nearfield ? tile_table_kernel<true> : tile_table_kernel<false>;
             hipLaunchKernelGGL(kern, dim3(p->num_tiles), dim3(W * dmas::kWaveSize), 0, nullptr, p->d_mic, p->d_dirs,
-                               p->d_tiles, M, p->fs, p->c, p->halo, p->mic_block, p->row, p->d_tile_off,
+                               p->d_tiles, M, p->fs, p->c, p->range, p->mic_block, p->row, p->d_tile_off,
                                p->d_tile_dref);
             e = hipGetLastError();
             if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -895,9 +934,9 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     }
     if (std::getenv("DMAS_LOG"))
         fprintf(stderr,
-                "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d row=%d mb=%d seg=%d/%d nseg=%d/%d lds=%zu/%zu "
+                "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d range=%d row=%d mb=%d seg=%d/%d nseg=%d/%d lds=%zu/%zu "
                 "occupancy=%d/%d\n",
-                M, T, D, n, p->num_tiles, p->halo, p->row, p->mic_block, p->seg_rf, p->seg_env, p->nseg_rf,
+                M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_rf, p->seg_env, p->nseg_rf,
                 p->nseg_env, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env);
     *out = p;
     return DMAS_OK;

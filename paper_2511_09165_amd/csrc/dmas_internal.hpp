@@ -30,15 +30,16 @@ struct KernelParams {
     const int32_t *tile_dirs; // num_tiles x dirs_per_tile direction indices (-1 = empty), device
     const int32_t *tile_off;  // optional, num_tiles x dirs_per_tile x M: LDS element where
                               // each direction's window of each microphone starts,
-                              // (mic % mic_block) * row + clamp(delay - reference + halo, 0, 2 halo)
-    const int32_t *tile_dref; // optional, num_tiles x M: reference (first direction) delays
+                              // (mic % mic_block) * row + (delay - the window's start)
+    const int32_t *tile_dref; // optional, num_tiles x M: the delays the windows start at
     const float *taps;        // fir_len envelope taps, device
     int32_t M, T, D;
     int32_t order;            // n
     int32_t fir_len;          // odd
     int32_t num_tiles;
     int32_t seg_len;          // output samples per direction per workgroup
-    int32_t halo;             // bound on |delay - reference delay| within a tile
+    int32_t halo;             // how far windows start before the reference delay: the bound on
+                              // |delay - reference delay| within a tile; 0 with tables
     int32_t row;              // LDS row length per microphone (floats)
     int32_t mic_block;        // microphones per LDS block, <= kMaxMicBlock
     int32_t dtype;            // dmas_dtype_t

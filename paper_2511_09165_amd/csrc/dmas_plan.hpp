@@ -38,7 +38,8 @@ struct dmas_plan_s {
     float cf_eps = 0;
     int fir_len = 0;
     int num_tiles = 0;
-    int halo = 0;
+    int halo = 0;          // largest |delay - reference direction's| within a tile
+    int range = 0;         // largest range of a microphone's delays within a tile
     int mic_block = 0;
     int row = 0;
     bool two_pass = false; // envelope calls: RF image into the output, then the filter over it in place
@@ -106,7 +107,7 @@ inline KernelParams make_params(const dmas_plan_s *plan, const void *d_x, const 
     kp.fir_len = env ? plan->fir_len : 1;
     kp.num_tiles = plan->num_tiles;
     kp.seg_len = env ? plan->seg_env : plan->seg_rf;
-    kp.halo = plan->halo;
+    kp.halo = plan->tables ? 0 : plan->halo;   // tables hold the window starts
     kp.row = plan->row;
     kp.mic_block = plan->mic_block;
     kp.dtype = plan->dtype;
