@@ -560,6 +560,19 @@ __device__ __forceinline__ float fp32_out_scale(const KernelParams &p)
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
 
+// One (root, sample) pair from LDS by an 8-byte read of its own (volatile, so
+// that the compiler does not pair reads into ds_read2st64_b64): 64 lanes of
+// ds_read_b64 come back at 230 bytes per clock and CU, paired reads at 125,
+// which bounded the kernels of orders up to 3 (measured by a probe; the
+// 1024-microphone near-field frame 33.9 -> 29.9 ms, 517 microphones at order 2
+// 128 -> 115 us, RF at order 3 84 -> 79 us, order 5 and up 0-1.5 %).
+__device__ __forceinline__ float2 lds_pair(const float2 *p)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const v2f v = *(const volatile __attribute__((address_space(3))) v2f *)p;
+    return make_float2(v.x, v.y);
+}
+
 // Barrier for LDS traffic alone: global stores in flight (the previous chunk's
 // outputs) are not waited for.
 __device__ __forceinline__ void lds_barrier()
@@ -929,7 +942,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                     if constexpr (ROOTS) {
                         float2 v[K];
 #pragma unroll
-                        for (int j = 0; j < K; ++j) v[j] = src[kWaveSize * j];
+                        for (int j = 0; j < K; ++j) v[j] = lds_pair(src + kWaveSize * j);
 #pragma unroll
                         for (int j = 0; j < K; ++j) {
                             if constexpr (FIRST) accumulate_root_first<N, CF, ACC>(acc[j], v[j].x, v[j].y);
