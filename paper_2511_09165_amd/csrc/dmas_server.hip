@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/dmas.h"
+#include "dmas_fetch.hpp"
 #include "dmas_internal.hpp"
 #include "dmas_plan.hpp"
 #include "dmas_resident.hpp"
@@ -212,6 +213,7 @@ struct dmas_server_s {
     std::mutex mu;
     std::condition_variable cv_done;     // frame completions, for waiters
     std::condition_variable cv_work;     // new submissions, for the scheduler
+    dmas::HostFetch fetcher;             // copies of results into pageable memory
     std::thread worker;
     std::atomic<bool> stop{false};
     std::string worker_error;
@@ -898,6 +900,8 @@ dmas_status_t dmas_server_create(const dmas_server_desc_t *d, dmas_server_t *out
     for (hipStream_t st : s->streams)
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return fail_all(e, "stream warm-up");
     if ((e = hipStreamSynchronize(s->copy_stream)) != hipSuccess) return fail_all(e, "copy stream warm-up");
+    // not beside resident workers, which hold the compute units a copy kernel would need
+    if (!d->resident) (void)s->fetcher.start(s->device);   // without it fetch copies by hipMemcpy
     s->worker = std::thread([s] { s->run(); });
     *out = s;
     return DMAS_OK;
@@ -1017,7 +1021,7 @@ dmas_status_t dmas_server_fetch(dmas_server_t s, uint64_t ticket, float *h_out)
         bytes = f->out_bytes;
     }
     // The result stays allocated until the caller releases the ticket.
-    hipError_t e = hipMemcpy(h_out, src, bytes, hipMemcpyDeviceToHost);
+    hipError_t e = s->fetcher.copy(h_out, src, bytes);
     if (e != hipSuccess) return srv_fail(DMAS_ERR_DEVICE, hipGetErrorString(e));
     return DMAS_OK;
 }

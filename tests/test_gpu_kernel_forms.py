@@ -158,3 +158,34 @@ def test_fixed_scratch_that_holds_only_the_unpadded_plane(monkeypatch):
         out = plan.envelope_noalloc(x, torch.empty_like(ref))
         torch.cuda.synchronize()
         assert torch.equal(ref, out)
+
+
+@pytest.mark.parametrize("D,T", [(200, 700), (512, 1024), (640, 2048), (701, 3003)])
+def test_fetch_moves_whole_results(D, T):
+    """Results fetched from a server, below and above the size that goes by chunks (2 MiB exactly,
+    whole chunks, a ragged tail), from several threads at once: the standalone call's bits."""
+    import threading
+    from paper_2511_09165_amd import Server, plan_for_frame
+    f = synth.random_frame(np.random.default_rng(D + T), 4, D, T, 3)
+    _say(f"fetch D={D} T={T}")
+    with plan_for_frame(f) as plan, Server(256 << 20, staging=16 << 20) as srv:
+        ref = plan.envelope(torch.from_numpy(f.x_f32()).cuda()).cpu().numpy()
+        tickets = [srv.submit(plan, f.x_f32()) for _ in range(4)]
+        for t in tickets:
+            srv.wait(t, 30.0)
+        got = {}
+
+        def fetch(t):
+            got[t] = [srv.fetch(t) for _ in range(3)]
+
+        threads = [threading.Thread(target=fetch, args=(t,)) for t in tickets]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join(60.0)
+        assert len(got) == 4
+        for images in got.values():
+            for y in images:
+                np.testing.assert_array_equal(y, ref)
+        for t in tickets:
+            srv.release(t)
