@@ -9,9 +9,11 @@
 //
 // Bound: HBM (each sample read and written once) and the matrix cores, whose
 // FP32 products do not run beside one another's loads well: 4186 x 16384
-// samples take 139 us (3.9 TB/s), 94 us with the products left out (5.8 TB/s;
+// samples take 134 us (4.1 TB/s), 90 us with the products left out (6.1 TB/s;
 // a large copy reaches 5.1-5.4) and 80 us for the products alone. Loads one
-// step ahead and barriers that wait for LDS only brought it there from 190 us.
+// step ahead and barriers that wait for LDS only brought it there from 190 us;
+// a block's operand reads ahead of its products took another 2 us off small
+// images (361 x 4096: 10.8 -> 8.9 us).
 #include "dmas_internal.hpp"
 
 namespace dmas {
@@ -50,7 +52,8 @@ __device__ __forceinline__ void lds_barrier()
 // first 2H values kept from the step before) and stores [o0, o0 + kRowBlock);
 // the samples loaded ahead start at o0 + kRowBlock + H or in another row, so
 // no output is stored over a sample that is still to be loaded.
-// KS: K steps whose taps a lane keeps in registers (0: read per block).
+// KS: the K steps, with a lane's taps in registers (0: any number, taps read
+// per block).
 template <int KS>
 __global__ void __launch_bounds__(kRowThreads, 8)
 envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, int D, int T, int L)
@@ -94,7 +97,7 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
     const float *ha = tap_lds + kTapLead + g - c;   // hr[m - i] of K step kk at ha[4 kk]
     float a[KS > 0 ? KS : 1];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) a[kk] = kk < ks ? ha[4 * kk] : 0.0f;
+    for (int kk = 0; kk < KS; ++kk) a[kk] = ha[4 * kk];
 
     while (d < D) {
         // window index i holds |y[o0 - H + i]|
@@ -122,16 +125,13 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
             const v4f *rq = reinterpret_cast<const v4f *>(win + g * plane + (b >> 2) + 4 * c);
             v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
             if constexpr (KS > 0) {
+                v4f r[(KS + 3) / 4];   // all reads first
 #pragma unroll
-                for (int q = 0; q < (KS + 3) / 4; ++q) {
-                    if (4 * q >= ks) break;
-                    const v4f r = rq[q];
+                for (int q = 0; q < (KS + 3) / 4; ++q) r[q] = rq[q];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (4 * q + u >= ks) break;
-                        if (u & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * q + u], r[u], e1, 0, 0, 0);
-                        else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * q + u], r[u], e0, 0, 0, 0);
-                    }
+                for (int kk = 0; kk < KS; ++kk) {
+                    if (kk & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], r[kk >> 2][kk & 3], e1, 0, 0, 0);
+                    else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], r[kk >> 2][kk & 3], e0, 0, 0, 0);
                 }
             } else {
                 for (int q = 0; 4 * q < ks; ++q) {
@@ -184,7 +184,8 @@ hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int
     const size_t lds = sizeof(float) * (size_t)(row_floats(H) + kRowWaves * kRowStage + env_taps_len(H));
     // workgroups for eight a CU (their LDS and registers allow eight)
     const unsigned grid = (unsigned)(D < 8 * cus ? D : 8 * cus);
-    auto kern = env_ksteps(H) <= 20 ? envelope_rows_kernel<20> : envelope_rows_kernel<0>;
+    // 20 K steps: 63 (the default) and 65 taps
+    auto kern = env_ksteps(H) == 20 ? envelope_rows_kernel<20> : envelope_rows_kernel<0>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, stream, img, taps, D, T, L);
     return hipGetLastError();
 }

@@ -23,7 +23,7 @@ def _image(f, x, out=None, **kw):
         return y.cpu().numpy()
 
 
-@pytest.mark.parametrize("L", [1, 63, 65, 67, 255])          # 65 is the last length with its taps in registers
+@pytest.mark.parametrize("L", [1, 63, 65, 67, 255])          # 63 and 65 keep their taps in registers
 @pytest.mark.parametrize("D,T", [(21, 1), (21, 33), (13, 2047), (13, 2048), (13, 2049), (9, 4100), (7, 5003),
                                  (2100, 70)])                # steps of 2048; more rows than workgroups
 def test_envelope_in_two_passes_gives_the_fused_bits(L, D, T, monkeypatch):
