@@ -317,25 +317,27 @@ bool direct_roots_pay(const dmas_plan_s *p)
 // Whether an envelope call runs as two passes: the RF image into the output,
 // then the filter over its rows in place (the same bits as the fused kernel).
 // The fused kernel's workgroups each walk long segments (a cut recomputes the
-// filter's halo), so a launch of few device rounds ends unevenly, and starts
-// with every workgroup staging and summing in step; RF workgroups take 1-3
-// chunks. Measured over frames of 8-780 microphones: the fused form loses
-// about a fifth of the RF time below three device rounds, while the second
-// pass costs 0.6 ps per pixel more than the fused filter (2.0 against 1.4 at
-// 4186 x 16384 pixels) and a launch of about 4 us. 64 microphones, 1035 x 8192
-// at order 3: 133 -> 121 us; 517 microphones, 361 x 4096 at order 2: 225 ->
-// 166 us; but 32 microphones, 4186 x 16384 at order 5 (5.5 rounds): 528 ->
-// 558 us, and 30 microphones, 145 x 14067 at order 3: 34 -> 46 us. RF
-// launches of fewer than two workgroups per compute unit are no better spread.
+// filter's halo), so its launch ends unevenly and starts with every workgroup
+// staging and summing in step, and its registers and rings cost occupancy; RF
+// workgroups take 1-3 chunks. Measured over 70 frames of 8-928 microphones,
+// the fused form loses about a fifth of the RF time, above order 5 three
+// tenths. An image that the 256 MB last-level cache holds until the second
+// pass reads it costs about 0.3 ps per pixel and a launch of 4 us more than
+// the fused filter; a larger one more than the fused form loses. 64
+// microphones, 1035 x 8192 at order 3: 143 -> 99 us; 517 microphones, 361 x
+// 4096 at order 2: 169 -> 116 us; 17 microphones, 6328 x 6131 at order 3: 216
+// -> 187 us; but 32 microphones, 4186 x 16384 at order 5 (274 MB): 506 -> 543
+// us, 14 microphones, 4656 x 4100 at order 2: 75 -> 85 us, and 25 microphones,
+// 578 x 6445 at order 5: 42 -> 45 us. RF launches of fewer than two
+// workgroups per compute unit are no better spread.
 bool two_pass_pays(const dmas_plan_s *p)
 {
+    constexpr double kImageInCache = 200 << 20;
     const double pixels = (double)p->D * p->T;
     const double slots = p->order + 2 + (p->linear ? 6 : 0);           // VALU slots per microphone and pixel
     const double rf = pixels * p->M * slots / 33e12 * (p->compensated ? 2 : 1);   // seconds
-    const int64_t wgs_rf = (int64_t)p->num_tiles * p->nseg_rf;
-    const int64_t wgs_env = (int64_t)p->num_tiles * p->nseg_env;
-    return wgs_rf >= 2 * (int64_t)p->cus && wgs_env < 3 * (int64_t)p->cus * std::max(1, p->occ_env) &&
-           0.2 * rf > 0.6e-12 * pixels + 4e-6;
+    return (int64_t)p->num_tiles * p->nseg_rf >= 2 * (int64_t)p->cus && 4 * pixels <= kImageInCache &&
+           (p->order > 5 ? 0.3 : 0.2) * rf > 0.3e-12 * pixels + 4e-6;
 }
 
 // Host estimate of fs*tau (tiling heuristics only; the kernels compute their own).
