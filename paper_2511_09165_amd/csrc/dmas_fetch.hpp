@@ -4,15 +4,21 @@
 // overlap. Twelve results of 53 MB in all, on warm and on fresh memory: one
 // thread's hipMemcpy 15 and 5-13 GB/s, four threads with 1 MiB chunks and a
 // stream each 28 and 10-24 GB/s (six or eight threads, 512 KiB or 2 MiB chunks
-// and one stream for all measured the same or slower).
+// and one stream for all measured the same or slower). Each thread maps its
+// chunk's pages while the chunk's DMA is under way: with a fresh array per
+// result, whose page faults cost more than the copies, the twelve results with
+// their kernels take 4.2 instead of 6.0 ms (2.8 on pages already mapped).
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstddef>
+#include <cstdint>
 #include <cstring>
 #include <mutex>
 #include <thread>
@@ -83,6 +89,7 @@ private:
             if (at >= bytes_) return;
             const size_t n = std::min(kChunk, bytes_ - at);
             hipError_t e = hipMemcpyAsync(buf, src_ + at, n, hipMemcpyDeviceToHost, streams_[i]);
+            if (e == hipSuccess) map_pages(dst_ + at, n);
             if (e == hipSuccess) e = hipStreamSynchronize(streams_[i]);
             if (e != hipSuccess) {
                 error_.store((int)e);
@@ -90,6 +97,19 @@ private:
             }
             std::memcpy(dst_ + at, buf, n);
         }
+    }
+
+    // Maps the pages of [p, p + n) for writing in one call, as the copy that
+    // follows would one fault at a time; where the kernel or the mapping does not
+    // support it the copy still does.
+    static void map_pages(char *p, size_t n)
+    {
+#ifdef MADV_POPULATE_WRITE
+        const uintptr_t at = reinterpret_cast<uintptr_t>(p), lo = at & ~((uintptr_t)sysconf(_SC_PAGESIZE) - 1);
+        (void)madvise(reinterpret_cast<void *>(lo), at + n - lo, MADV_POPULATE_WRITE);
+#else
+        (void)p, (void)n;
+#endif
     }
 
     void help(int i)
