@@ -12,17 +12,20 @@
 // design):
 //   * With whole-sample delays the root of a delayed sample is the root of a
 //     channel sample, so a separate pass (root_plane_kernel) writes each
-//     channel sample's (root, sample) pair once; the beamformer stages those.
+//     channel sample's (root, sample) pair once; the beamformer stages those
+//     (single calls of small frames take the roots while staging instead).
 //   * A workgroup owns one tile of kDirsPerTile nearby directions (one wave per
 //     direction) and one time segment. Directions were grouped on the host so
 //     that their steering delays stay within +-halo samples of the tile's first
 //     (reference) direction.
 //   * The segment is walked in chunks of kChunk samples. For each chunk the
 //     workgroup stages, per microphone, one window
-//     [t0 + d_ref - halo, t0 + d_ref - halo + row) into LDS (zero outside the
-//     record); every wave then reads its own delayed samples from that window
-//     with a wave-uniform offset, so one staged window serves all directions
-//     of the tile. Microphones are staged in blocks of <= 64 when M is large.
+//     [t0 + start, t0 + start + row) into LDS (zero outside the record; start
+//     is the tile's smallest delay with tables, the reference direction's
+//     minus the halo otherwise); every wave then reads its own delayed samples
+//     from that window with a wave-uniform offset, so one staged window serves
+//     all directions of the tile. Microphones are staged in blocks of <= 64
+//     (<= 16 with per-block tables).
 //   * Window offsets come from per-tile tables built at plan creation (read
 //     through the scalar cache when small) or are computed from the geometry.
 //   * Each lane owns kSamplesPerLane output samples at stride 64 and keeps
@@ -31,11 +34,13 @@
 //     is one scalar offset shared by all samples of the lane.
 //   * The epilogue evaluates Newton-Girard, CF and either stores y, or writes
 //     |y| into a per-wave LDS ring; the ring keeps the last L-1 values between
-//     chunks so the envelope never round-trips through HBM and needs only L-1
-//     samples of halo per segment.
+//     chunks so the envelope makes no round trip through HBM and needs only
+//     L-1 samples of halo per segment. (Where a pass over the image costs less
+//     than that, the plan stores y and a second kernel filters the image.)
 //   * The microphone loop is a gather and sum, not a contraction, and runs on
-//     the VALU (its bound); the envelope FIR of a chunk is a Toeplitz matrix
-//     product and runs on the matrix cores in FP32.
+//     the VALU (its bound, with the LDS reads at orders up to 3); the envelope
+//     FIR of a chunk is a Toeplitz matrix product and runs on the matrix cores
+//     in FP32.
 #pragma once
 
 #include <hip/hip_bf16.h>
@@ -513,9 +518,6 @@ __device__ __forceinline__ R newton_girard(const R *P)
     return newton_girard_scaled<N, R>(P) * R(ng_scale(N));
 }
 
-// One output pixel from its sums: y = E_n * CF * in_scale, eqs. (13)/(14).
-// In the FP32 form the 1/n! of the expansions is folded into `out_scale`
-// (in_scale / n!, formed once per kernel by the caller).
 // One output pixel from its sums: y = E_n * CF * in_scale, eqs. (13)/(14).
 // Newton-Girard runs in FP64 for FP64 sums or with the plan's ng_fp64 flag
 // (its result, n! E_n for n <= 5, is rounded to FP32 once the cancellation
