@@ -49,6 +49,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "dmas.h"
 #include "dmas_internal.hpp"
 
 namespace dmas {
@@ -302,25 +303,46 @@ __device__ __forceinline__ void stage_row_roots(float2 *__restrict__ dst, const 
     }
 }
 
-// The same window with the roots taken while staging, from the channels
+// The same windows with the roots taken while staging, from the channels
 // themselves: for small frames, whose root pass and plane (allocated around
-// the call) take longer than the roots of every window.
+// the call) take longer than the roots of every window. Row k < rows (at most
+// two a wave) is the window [base[k], base[k] + row) of the channel at chan[k].
+// Such frames put one or two workgroups on a compute unit and are bound by the
+// latency of one: the loads of both rows are issued before the first root, from
+// indices clamped into the record. (One row and four masked loads at a time put
+// four latencies in a row, 4000 clocks a block: 40 microphones, 120 x 3000 at
+// order 5 15.4 -> 12.9 us, 64, 90 x 2000 at order 3 17.3 -> 16.2, 19, 181 x 3001
+// at order 3 11.4 -> 11.0, 24, 288 x 4000 20.0 -> 19.7. Five pieces of a row
+// without the branch each are up to 6 % faster on sweeps of one angle and up to
+// 6 % slower on grids of two.)
 template <int N, int DT>
-__device__ __forceinline__ void stage_row_direct(float2 *__restrict__ dst, const void *__restrict__ x, size_t chan,
-                                                 int base, int row, int T, int lane)
+__device__ __forceinline__ void stage_rows_direct(float2 *const (&dst)[2], const void *__restrict__ x,
+                                                  const size_t (&chan)[2], const int (&base)[2], int rows, int row,
+                                                  int T, int lane)
 {
-    constexpr int U = 4;   // loads in flight per lane
+    constexpr int U = 6;   // pieces of 64 in flight per row
     for (int r0 = 0; r0 < row; r0 += U * kWaveSize) {
-        float v[U];
+        float v[2][U];
 #pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const int r = r0 + kWaveSize * j + lane, t = base + r;
-            v[j] = (r < row && t >= 0 && t < T) ? load_sample<DT>(x, chan + (size_t)t) : 0.0f;
+        for (int k = 0; k < 2; ++k) {
+            if (k >= rows) break;
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                if (r0 + kWaveSize * j >= row) break;   // wave-uniform
+                const int t = base[k] + r0 + kWaveSize * j + lane;
+                v[k][j] = load_sample<DT>(x, chan[k] + (size_t)(unsigned)min(max(t, 0), T - 1));
+            }
         }
 #pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const int r = r0 + kWaveSize * j + lane;
-            if (r < row) dst[r] = make_float2(signed_root<N, true>(v[j]), v[j]);
+        for (int k = 0; k < 2; ++k) {
+            if (k >= rows) break;
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                if (r0 + kWaveSize * j >= row) break;   // wave-uniform
+                const int r = r0 + kWaveSize * j + lane, t = base[k] + r;
+                const float xv = t >= 0 && t < T ? v[k][j] : 0.0f;
+                if (r < row) dst[k][r] = make_float2(signed_root<N, true>(xv), xv);
+            }
         }
     }
 }
@@ -612,6 +634,15 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
     using Elem = typename std::conditional<ROOTS, float2, float>::type;
 
     const int H = ENV ? (p.fir_len - 1) / 2 : 0;
+    // Entry j of the taps table, the taps reversed: entry kTapLead + k holds h[2H - k].
+    auto tap_entry = [&](int j) {
+        const int k = j - kTapLead;
+        return (k >= 0 && k <= 2 * H) ? p.taps[2 * H - k] : 0.0f;
+    };
+    static_assert(env_taps_len((DMAS_MAX_FIR_LEN - 1) / 2) <= W * kWaveSize, "at most one entry a thread");
+    // (latency-bound launches: the load is under way while the rest is set up)
+    float tap_early = 0.0f;
+    if constexpr (ENV && takes_roots(DM)) tap_early = tap_entry(tx);
     // LDS: the window region (mic_block x row windows; with `share` also the
     // per-wave rings in the envelope epilogue), reference delays, taps table,
     // then per wave either its ring or (share) the |y| it carries between chunks
@@ -727,6 +758,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
         sdref0 = dref_row[r0];
         sdref1 = dref_row[r0 + W];
     };
+    if constexpr (takes_roots(DM)) load_drefs(0);
     auto load_offsets = [&](int blk) {
         const_i32 *ob = off_srow + blk * p.mic_block;
 #pragma unroll
@@ -751,9 +783,6 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
         }
     };
 
-    // Copy the taps' positions: the FIR reads them through the scalar cache.
-    const float *__restrict__ taps = p.taps;
-
     if (all_mics) block_geometry(0);
     if constexpr (ENV) {
         if constexpr (share) {
@@ -761,10 +790,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
         } else {
             for (int i = lane; i < ring_stride(H); i += kWaveSize) ring[i] = 0.0f;
         }
-        for (int j = tx; j < env_taps_len(H); j += W * kWaveSize) {
-            const int k = j - kTapLead;   // reversed: entry kTapLead + k holds h[2H - k]
-            tap_lds[j] = (k >= 0 && k <= 2 * H) ? taps[2 * H - k] : 0.0f;
-        }
+        if (tx < env_taps_len(H)) tap_lds[tx] = takes_roots(DM) ? tap_early : tap_entry(tx);
         // the first block's barrier makes the taps table visible before any epilogue
     }
 
@@ -865,7 +891,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
     };
 
     const float out_scale = fp32_out_scale<N>(p);
-    if constexpr (TAB_BLOCKS) load_drefs(0);
+    if constexpr (TAB_BLOCKS && !takes_roots(DM)) load_drefs(0);
 
     // Power sums. Plain FP32 sums (PEEL): each chunk's first microphone starts
     // them, so they are the pass's own (nothing carried from one pass to the
@@ -896,19 +922,26 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
             // (issued at normal wave priority: raising it helped the loads
             // through registers by 0.9 % on the 1024-microphone frame, but costs
             // 0.5-0.9 % with the global-to-LDS copies)
-            for (int i = wave; i < p.mic_block; i += W) {
+            if constexpr (takes_roots(DM)) {
+                static_assert(table_block_max(N) <= 2 * W, "a wave stages at most two rows of a block");
+                const int m0 = blk * p.mic_block + wave, m1 = m0 + W;
+                const int rows = wave >= p.mic_block || m0 >= p.M ? 0 : wave + W < p.mic_block && m1 < p.M ? 2 : 1;
+                float2 *const dst[2] = {xwin + wave * p.row, xwin + (wave + W) * p.row};
+                const size_t chan[2] = {(size_t)m0 * (size_t)p.T, (size_t)m1 * (size_t)p.T};
+                const int base[2] = {tc + sdref0 - p.halo, tc + sdref1 - p.halo};
+                if (p.dtype == 0) stage_rows_direct<N, 0>(dst, p.x, chan, base, rows, p.row, p.T, lane);
+                else if (p.dtype == 1) stage_rows_direct<N, 1>(dst, p.x, chan, base, rows, p.row, p.T, lane);
+                else stage_rows_direct<N, 2>(dst, p.x, chan, base, rows, p.row, p.T, lane);
+            }
+            for (int i = wave; i < (takes_roots(DM) ? 0 : p.mic_block); i += W) {
                 const int mic = blk * p.mic_block + i;
                 Elem *dst = xwin + i * p.row;
                 if (mic < p.M) {
                     const int base = tc + dref_of(blk, i) - p.halo;
                     const size_t chan = (size_t)mic * (size_t)p.T;
                     if constexpr (ROOTS) {
-                        if constexpr (!takes_roots(DM))
-                            stage_row_roots(dst, p.roots + (size_t)mic * (size_t)p.plane_stride, base, p.row, p.plane_lo,
-                                            p.plane_hi, p.T, lane);
-                        else if (p.dtype == 0) stage_row_direct<N, 0>(dst, p.x, chan, base, p.row, p.T, lane);
-                        else if (p.dtype == 1) stage_row_direct<N, 1>(dst, p.x, chan, base, p.row, p.T, lane);
-                        else stage_row_direct<N, 2>(dst, p.x, chan, base, p.row, p.T, lane);
+                        stage_row_roots(dst, p.roots + (size_t)mic * (size_t)p.plane_stride, base, p.row, p.plane_lo,
+                                        p.plane_hi, p.T, lane);
                     } else {
                         if (p.dtype == 0) stage_row<0>(dst, p.x, chan, base, p.row, p.T, lane);
                         else if (p.dtype == 1) stage_row<1>(dst, p.x, chan, base, p.row, p.T, lane);
