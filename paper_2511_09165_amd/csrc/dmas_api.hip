@@ -300,44 +300,50 @@ void plane_pads(const dmas_plan_desc_t *d, double c, int chunk, dmas_plan_s *p)
 }
 
 // Whether a single call takes the roots while staging instead of reading them
-// from a root plane (the same bits). The plane costs a launch (2-3 us) and a
-// pool allocation and free around the call (about 15 us of host time, which
-// bounds calls whose kernels are shorter); without it a sample's root is taken
-// again in every window that holds it, work that grows with the pixels and
-// microphones. Measured (back to back): 8 microphones, 64 x 1024 at order 2
-// 26.4 -> 10.2 us, 19, 181 x 3001 at order 3 30.9 -> 12.0 us, 18, 351 x 7669
-// at order 6 (4.9e7 pixel-microphones) 30.1 -> 26.2 us, 30, 145 x 14067 at
-// order 3 (6.1e7) 33.9 -> 31.2 us, but 20, 2211 x 1836 at order 7 (8.1e7)
-// 61.8 -> 67.0 us and 25, 2450 x 3037 at order 3 (1.9e8) 42.5 -> 46.8 us.
+// from a root plane (the same bits). The plane costs a launch (2-3 us) and a pool
+// allocation and free around the call (about 15 us of host time, which bounds
+// calls whose kernels are shorter than 30 us); without it a sample's root is
+// taken again in every window that holds it, work that grows with the windows'
+// elements, and every block of 16 microphones waits for its loads in turn.
+// Measured over 45 frames (back to back, plane against direct): 8 microphones, 64
+// x 1024 at order 2 33.0 and 9.9 us, 19, 181 x 3001 at order 3 25.1 and 11.6, 57,
+// 78 x 4725 at order 6 29.9 and 16.9, 30, 145 x 14067 at order 3 (6.5e7 elements)
+// 32.6 and 28.1; but 58, 210 x 4619 at order 3 (1.0e8) 42.2 and 45.6, 25, 2450 x
+// 3037 at order 3 (2e8) 58.6 and 68.7, and 241, 77 x 1408 at order 5 (3.2e7, 16
+// blocks) 48.6 and 53.4.
 bool direct_roots_pay(const dmas_plan_s *p)
 {
-    return (double)p->M * p->D * p->T < 7e7;
+    const double elements =
+        (double)p->M * p->num_tiles * dmas::kDirsPerTile * p->T * (dmas::kChunk + p->range) / dmas::kChunk;
+    return p->M <= 128 && elements < 9e7;
 }
 
-// Whether an envelope call runs as two passes: the RF image into the output,
-// then the filter over its rows in place (the same bits as the fused kernel).
-// The fused kernel's workgroups each walk long segments (a cut recomputes the
+// Whether an envelope call runs as two passes: the RF image into the output, then
+// the filter over its rows in place (the same bits as the fused kernel). The
+// fused kernel's workgroups each walk long segments (a cut recomputes the
 // filter's halo), so its launch ends unevenly and starts with every workgroup
 // staging and summing in step, and its registers and rings cost occupancy; RF
-// workgroups take 1-3 chunks. Measured over 70 frames of 8-928 microphones,
-// the fused form loses about a fifth of the RF time, above order 5 three
-// tenths. An image that the 256 MB last-level cache holds until the second
-// pass reads it costs about 0.3 ps per pixel and a launch of 4 us more than
-// the fused filter; a larger one more than the fused form loses. 64
-// microphones, 1035 x 8192 at order 3: 143 -> 99 us; 517 microphones, 361 x
-// 4096 at order 2: 169 -> 116 us; 17 microphones, 6328 x 6131 at order 3: 216
-// -> 187 us; but 32 microphones, 4186 x 16384 at order 5 (274 MB): 506 -> 543
-// us, 14 microphones, 4656 x 4100 at order 2: 75 -> 85 us, and 25 microphones,
-// 578 x 6445 at order 5: 42 -> 45 us. RF launches of fewer than two
-// workgroups per compute unit are no better spread.
+// workgroups take 1-3 chunks. Measured over 70 frames of 8-928 microphones, the
+// fused form loses about a fifth of the RF time, above order 5 three tenths, with
+// linear delays half of that (18 microphones, 1953 x 5673 at order 3: 108 against
+// 109 us in two passes). An image that the 256 MB last-level cache holds until
+// the second pass reads it costs about 0.3 ps per pixel and a launch of 4 us more
+// than the fused filter; a larger one more than the fused form loses. 64
+// microphones, 1035 x 8192 at order 3: 143 -> 99 us; 517 microphones, 361 x 4096
+// at order 2: 169 -> 116 us; 17 microphones, 6328 x 6131 at order 3: 216 -> 187
+// us; but 32 microphones, 4186 x 16384 at order 5 (274 MB): 506 -> 543 us, 14
+// microphones, 4656 x 4100 at order 2: 75 -> 85 us, and 25 microphones, 578 x
+// 6445 at order 5: 42 -> 45 us. RF launches of fewer than two workgroups per
+// compute unit are no better spread.
 bool two_pass_pays(const dmas_plan_s *p)
 {
     constexpr double kImageInCache = 200 << 20;
     const double pixels = (double)p->D * p->T;
     const double slots = p->order + 2 + (p->linear ? 6 : 0);           // VALU slots per microphone and pixel
     const double rf = pixels * p->M * slots / 33e12 * (p->compensated ? 2 : 1);   // seconds
+    const double loss = (p->order > 5 ? 0.3 : 0.2) * (p->linear ? 0.5 : 1.0);
     return (int64_t)p->num_tiles * p->nseg_rf >= 2 * (int64_t)p->cus && 4 * pixels <= kImageInCache &&
-           (p->order > 5 ? 0.3 : 0.2) * rf > 0.3e-12 * pixels + 4e-6;
+           loss * rf > 0.3e-12 * pixels + 4e-6;
 }
 
 // Host estimate of fs*tau (tiling heuristics only; the kernels compute their own).
