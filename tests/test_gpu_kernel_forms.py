@@ -103,6 +103,29 @@ def test_direct_roots_with_other_sums(accumulate, n, monkeypatch):
     check_t1(got["1"], oracle.envelope(y_ref, taps))
 
 
+@pytest.mark.parametrize("T", [1, 63, 900])
+@pytest.mark.parametrize("spread", [0.004, 0.05, 0.15, 0.4])
+@pytest.mark.parametrize("M", [3, 8, 9, 16, 25])
+def test_direct_rows_and_record_ends(M, spread, T, monkeypatch):
+    """No, one or two rows a wave, windows of one to several rounds of loads (five pieces of 64 and
+    up), and records shorter than a window: the bits of the root plane. The first and last samples
+    are not finite, so a sample taken from outside its place shows."""
+    from paper_2511_09165_amd import plan_for_frame
+    f = synth.random_frame(np.random.default_rng(100 * M + T), M, 19, T, 3)
+    f.mic_pos = f.mic_pos * (spread / np.abs(f.mic_pos).max())
+    x = f.x_f32().copy()
+    x[0, 0], x[1, T - 1], x[M - 1, 0] = np.inf, np.nan, -np.inf
+    _say(f"direct rows M={M} spread={spread} T={T}")
+    got = {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        with plan_for_frame(f) as plan:
+            xt = torch.from_numpy(x).cuda()
+            got[direct] = [plan.beamform(xt).cpu().numpy(), plan.envelope(xt).cpu().numpy()]
+    for a, b in zip(got["0"], got["1"]):
+        np.testing.assert_array_equal(a, b)
+
+
 def test_direct_plan_in_a_graph_and_on_two_streams():
     """A plan without a root plane replays from a graph, with eager calls between, and runs on two
     streams at once: every result equals the eager one."""
