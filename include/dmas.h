@@ -197,8 +197,10 @@ dmas_status_t dmas_beamform(dmas_plan_t plan, const void *d_x, float *d_y,
 /* DMAS-n (+CF) image followed by envelope detection, in the same kernel or
  * (plans without decimation, where it is faster) in a second one that filters
  * the RF image in d_env in place: writes d_env (D x ceil(T/k) FP32, device;
- * k = env_decimation). Arguments, root plane and errors as for
- * dmas_beamform. */
+ * k = env_decimation). Both give the same bits, also for pixels that are not
+ * finite: such a pixel makes NaN of the outputs whose taps hold it, and
+ * possibly of up to 17 outputs before and 15 after those. Arguments, root plane
+ * and errors as for dmas_beamform. */
 dmas_status_t dmas_envelope(dmas_plan_t plan, const void *d_x, float *d_env,
                             float in_scale, void *stream);
 

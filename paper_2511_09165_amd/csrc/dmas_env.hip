@@ -5,7 +5,12 @@
 // The same 16 x 16 Toeplitz products in FP32 on the matrix cores, in the same
 // K order, as the beamformer's fused epilogue (dmas_kernel.hpp): an output's
 // products depend on its time index modulo 16 only, so both forms give the
-// same bits.
+// same bits. That includes samples that are not finite. The products of a
+// block of 16 outputs run over 2H + 16 samples, for odd H over 2H + 18, and so
+// multiply samples outside an output's taps by zero, which a NaN or infinity
+// turns into NaN: up to 17 outputs before and 15 after those whose taps hold it.
+// Where the fused kernel has a zero in place of such a sample (past the end of
+// its chunk), this one takes a zero too (products below).
 //
 // Bound: HBM (each sample read and written once) and the matrix cores, whose
 // FP32 products do not run beside one another's loads well: 4186 x 16384
@@ -25,12 +30,14 @@ constexpr int kRowWaves = kRowThreads / kWaveSize;
 constexpr int kRowBlock = 2048;   // outputs of one walk step
 static_assert(kRowBlock % (kChunk * kRowWaves) == 0, "each wave takes whole output blocks");
 
-// LDS window of a walk step: |y| of indices [0, kRowBlock + 2H) and zeros up
-// to the last index that the FIR's K steps read. Index i lies in plane i % 4
+// LDS window of a walk step: |y| of indices [0, kRowBlock + 2H + kPast), which
+// are all that the FIR's K steps use (kPast: those past the last output's
+// taps), and zeros up to the last index that is read. Index i lies in plane i % 4
 // at i / 4: a lane's operand of K steps 4q .. 4q + 3 is then 16 consecutive
 // bytes (one ds_read_b128 instead of four 4-byte reads), and the planes lie
 // 16 banks apart, so that both those reads and the element-wise fill, 64
 // consecutive indices a wave, fall on distinct banks.
+constexpr int kPast = 2;
 __host__ __device__ constexpr int row_logical(int H) { return kRowBlock + 2 * H + 24; }
 __host__ __device__ constexpr int row_plane(int H) { return ((row_logical(H) / 4 + 1 + 63) & ~63) + 16; }
 __host__ __device__ constexpr int row_floats(int H) { return 4 * row_plane(H); }
@@ -48,15 +55,18 @@ __device__ __forceinline__ void lds_barrier()
 
 // A workgroup walks whole rows, blockIdx.x and every gridDim.x-th after it, in
 // steps of kRowBlock outputs, and loads the next step's samples while it works
-// on this one's. The step at o0 holds |y| of [o0 - H, o0 + kRowBlock + H) (its
-// first 2H values kept from the step before) and stores [o0, o0 + kRowBlock);
-// the samples loaded ahead start at o0 + kRowBlock + H or in another row, so
-// no output is stored over a sample that is still to be loaded.
+// on this one's. The step at o0 holds |y| of [o0 - H, o0 + kRowBlock + H +
+// kPast) (its first 2H + kPast values kept from the step before) and stores
+// [o0, o0 + kRowBlock); the samples loaded ahead start at o0 + kRowBlock + H +
+// kPast or in another row, so no output is stored over a sample that is still
+// to be loaded. seg_len: the fused kernel's outputs per segment (a multiple of
+// 32), seg_inv = floor((2^32 - 1) / (seg_len / 32)).
 // KS: the K steps, with a lane's taps in registers (0: any number, taps read
 // per block).
 template <int KS>
 __global__ void __launch_bounds__(kRowThreads, 8)
-envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, int D, int T, int L)
+envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, int D, int T, int L, int seg_len,
+                     uint32_t seg_inv)
 {
     typedef float v4f __attribute__((ext_vector_type(4)));
     extern __shared__ float smem[];
@@ -72,18 +82,20 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
     const int ks = env_ksteps(H);
     auto at = [&](int i) { return (i & 3) * plane + (i >> 2); };
 
-    // new samples of a step: t = o0 + H + j * kRowThreads + tid; the first step
-    // of a row also has samples 0 .. H - 1 (H < kRowThreads)
+    const int keep_len = 2 * H + kPast;   // <= kRowThreads
+
+    // new samples of a step: t = o0 + H + kPast + j * kRowThreads + tid; the first
+    // step of a row also has samples 0 .. H + kPast - 1
     constexpr int kLoads = kRowBlock / kRowThreads;
     float v[kLoads], head = 0.0f;
     auto fetch = [&](int d, int o0) {
         const float *src = img + (size_t)d * (size_t)T;
 #pragma unroll
         for (int j = 0; j < kLoads; ++j) {
-            const int t = o0 + H + j * kRowThreads + tid;
+            const int t = o0 + H + kPast + j * kRowThreads + tid;
             v[j] = t < T ? src[t] : 0.0f;
         }
-        if (o0 == 0) head = tid >= H && tid < 2 * H && tid - H < T ? src[tid - H] : 0.0f;
+        if (o0 == 0) head = tid >= H && tid < keep_len && tid - H < T ? src[tid - H] : 0.0f;
     };
     int d = blockIdx.x, o0 = 0;
     if (d < D) fetch(d, 0);
@@ -92,23 +104,63 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
         const int k = j - kTapLead;   // reversed: entry kTapLead + k holds h[2H - k]
         tap_lds[j] = (k >= 0 && k <= 2 * H) ? taps[2 * H - k] : 0.0f;
     }
-    for (int i = kRowBlock + 2 * H + tid; i < row_logical(H); i += kRowThreads) win[at(i)] = 0.0f;
+    for (int i = kRowBlock + keep_len + tid; i < row_logical(H); i += kRowThreads) win[at(i)] = 0.0f;
     lds_barrier();
     const float *ha = tap_lds + kTapLead + g - c;   // hr[m - i] of K step kk at ha[4 kk]
     float a[KS > 0 ? KS : 1];
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) a[kk] = ha[4 * kk];
 
+    // Products of the wave's block of 256 outputs at t0, window operands at rq, taps
+    // read again. The operand of the last K step: where the fused kernel has a zero
+    // in place of the sample that K row 3 holds, the first one past the chunk that
+    // yields the 16 outputs, a zero too. A segment at g0 walks chunks from
+    // max(g0 - lead, 0); a chunk's last outputs reach past it only if H + 1 is a
+    // multiple of 32 (= lead). That sample's tap is zero, so it matters only where
+    // it is not finite, and then all 16 outputs are not.
+    const bool reaches = ((H + 1) & 31) == 0;
+    auto products = [&](const v4f *rq, int t0) {
+        int me = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(me));   // lane values formed here: kept from above they cost registers
+        const int g = me >> 4, c = me & 15;
+        const float *ha = tap_lds + kTapLead + g - c;
+        v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
+        constexpr int U = KS > 0 ? 1 : 4;   // (with KS > 0 rare, and so it takes few registers)
+#pragma unroll 1
+        for (int k0 = 0; k0 < ks; k0 += U) {
+            v4f four = {};
+            if constexpr (U == 4) four = rq[k0 >> 2];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int kk = k0 + u;
+                if (kk >= ks) break;
+                float r = U == 4 ? four[u] : reinterpret_cast<const float *>(rq)[kk];
+                if (kk == ks - 1 && reaches && __builtin_amdgcn_ballot_w64(!(r <= __FLT_MAX__)) != 0) {
+                    const int tb = t0 + 16 * c, lead = env_lead(H);
+                    const uint32_t n = (uint32_t)tb >> 5, len = (uint32_t)seg_len >> 5;
+                    uint32_t seg = __umulhi(n, seg_inv);   // n / len or one less
+                    if (n - seg * len >= len) ++seg;
+                    const int start = max((int)seg * seg_len - lead, 0);
+                    if (g == 3 && ((tb + lead + 16 - start) & (kChunk - 1)) == 0) r = 0.0f;
+                }
+                const v4f e = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[4 * kk], r, kk & 1 ? e1 : e0, 0, 0, 0);
+                if (kk & 1) e1 = e;
+                else e0 = e;
+            }
+        }
+        return e0 + e1;
+    };
+
     while (d < D) {
         // window index i holds |y[o0 - H + i]|
-        float keep = __builtin_fabsf(head);            // indices 0 .. 2H - 1 (2H < kRowThreads)
+        float keep = __builtin_fabsf(head);            // indices 0 .. keep_len - 1
         if (o0 > 0) {
-            if (tid < 2 * H) keep = win[at(kRowBlock + tid)];
+            if (tid < keep_len) keep = win[at(kRowBlock + tid)];
             lds_barrier();
         }
-        if (tid < 2 * H) win[at(tid)] = keep;
+        if (tid < keep_len) win[at(tid)] = keep;
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) win[at(2 * H + j * kRowThreads + tid)] = __builtin_fabsf(v[j]);
+        for (int j = 0; j < kLoads; ++j) win[at(keep_len + j * kRowThreads + tid)] = __builtin_fabsf(v[j]);
         lds_barrier();
         float *row = img + (size_t)d * (size_t)T;
         const int o = o0;
@@ -123,8 +175,9 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
             // outputs o + b + q, q = 16j + i: F[i][j] = sum_m hr[m - i] r[16j + m], r = window
             // from b; lane l supplies r[16c + 4kk + g] and receives the outputs 16c + 4g ..+3
             const v4f *rq = reinterpret_cast<const v4f *>(win + g * plane + (b >> 2) + 4 * c);
-            v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
+            v4f e;
             if constexpr (KS > 0) {
+                v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
                 v4f r[(KS + 3) / 4];   // all reads first
 #pragma unroll
                 for (int q = 0; q < (KS + 3) / 4; ++q) r[q] = rq[q];
@@ -133,18 +186,14 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
                     if (kk & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], r[kk >> 2][kk & 3], e1, 0, 0, 0);
                     else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], r[kk >> 2][kk & 3], e0, 0, 0, 0);
                 }
+                e = e0 + e1;
+                // outputs that are not finite are formed again (a choice of the
+                // last operand before its product cost registers, 0.5-2.5 % of a call)
+                if (reaches && __builtin_amdgcn_ballot_w64(!(__builtin_fabsf(e[0]) <= __FLT_MAX__)) != 0)
+                    e = products(rq, o + b);
             } else {
-                for (int q = 0; 4 * q < ks; ++q) {
-                    const v4f r = rq[q];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (4 * q + u >= ks) break;
-                        if (u & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[16 * q + 4 * u], r[u], e1, 0, 0, 0);
-                        else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[16 * q + 4 * u], r[u], e0, 0, 0, 0);
-                    }
-                }
+                e = products(rq, o + b);
             }
-            const v4f e = e0 + e1;
             const int t0 = o + b;
             const int t = t0 + 16 * c + 4 * g;
             if ((reinterpret_cast<uintptr_t>(row) & 15) == 0) {   // wave-uniform
@@ -178,7 +227,8 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
 
 }  // namespace
 
-hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int L, int cus, hipStream_t stream)
+hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int L, int seg_len, int cus,
+                                hipStream_t stream)
 {
     const int H = (L - 1) / 2;
     const size_t lds = sizeof(float) * (size_t)(row_floats(H) + kRowWaves * kRowStage + env_taps_len(H));
@@ -186,7 +236,8 @@ hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int
     const unsigned grid = (unsigned)(D < 8 * cus ? D : 8 * cus);
     // 20 K steps: 63 (the default) and 65 taps
     auto kern = env_ksteps(H) == 20 ? envelope_rows_kernel<20> : envelope_rows_kernel<0>;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, stream, img, taps, D, T, L);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, stream, img, taps, D, T, L, seg_len,
+                       0xffffffffu / ((uint32_t)seg_len >> 5));
     return hipGetLastError();
 }
 

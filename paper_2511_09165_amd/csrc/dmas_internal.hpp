@@ -183,8 +183,10 @@ hipError_t launch_roots(int order, int dtype, const void *x, float2 *plane, int 
                         hipStream_t stream);
 
 // Envelope filter of an RF image (D rows of T samples) in place, for the plan's
-// taps on the device (L of them, zero-padded); cus: compute units of the device.
-hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int L, int cus, hipStream_t stream);
+// taps on the device (L of them, zero-padded); seg_len: the fused envelope
+// kernel's outputs per segment; cus: compute units of the device.
+hipError_t launch_envelope_rows(float *img, const float *taps, int D, int T, int L, int seg_len, int cus,
+                                hipStream_t stream);
 
 // Matched filter: out[i*T + t] = sum_{k<P} raw[i*T + t + k] * pulse[k].
 hipError_t launch_matched_filter(const float *raw, const float *pulse, int M, int T, int P, float *out,

@@ -172,7 +172,8 @@ inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const f
     hipError_t e = launch_plan(plan->order, &kp, plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused),
                                stream);
     if (e == hipSuccess && env && !fused)
-        e = launch_envelope_rows(d_out, plan->d_taps, plan->D, plan->T, plan->fir_len, plan->cus, stream);
+        e = launch_envelope_rows(d_out, plan->d_taps, plan->D, plan->T, plan->fir_len, plan->seg_env, plan->cus,
+                                 stream);
     return e;
 }
 
