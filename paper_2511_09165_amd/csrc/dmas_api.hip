@@ -262,21 +262,6 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
     }
 }
 
-// The same without an envelope: segments share nothing, so a cut costs only
-// the workgroup's setup.
-void choose_rf_segments(int T, int num_tiles, int64_t slots, int fixed, int *seg, int *nseg)
-{
-    int s = (fixed + 31) & ~31;
-    if (fixed <= 0) {
-        int chunks = 3;
-        while (chunks > 1 && (int64_t)num_tiles * ((T + chunks * dmas::kChunk - 1) / (chunks * dmas::kChunk)) < 4 * slots)
-            --chunks;
-        s = chunks * dmas::kChunk;
-    }
-    *seg = s;
-    *nseg = (T + s - 1) / s;
-}
-
 // Zero pairs around the rows of single calls' root planes, so that windows
 // reaching past the record's ends are copied like all others instead of
 // element by element, which took several times as long: workgroups at the ends
@@ -937,7 +922,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         if (env)
             choose_segments(T, p->num_tiles, H, slots, seg_override, &p->seg_env, &p->nseg_env);
         else
-            choose_rf_segments(T, p->num_tiles, slots, seg_override, &p->seg_rf, &p->nseg_rf);
+            dmas::choose_rf_segments(T, p->num_tiles, slots, seg_override, &p->seg_rf, &p->nseg_rf);
         if (env) p->occ_env = blocks; else p->occ_rf = blocks;
     }
     p->two_pass = decim == 1 && two_pass_pays(p);

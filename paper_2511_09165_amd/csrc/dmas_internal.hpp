@@ -100,6 +100,20 @@ constexpr int kDirsPerTile = 8;
 constexpr int kSamplesPerLane = 4;
 constexpr int kChunk = kWaveSize * kSamplesPerLane;
 
+// A launch has fewer than 2^32 threads in each grid dimension: the most
+// workgroups of the beamformer, and the root pass's grid for M rows of stride
+// pairs, where a workgroup of kRootThreads takes kRootBlock pairs of one row
+// (rows past grid_y go round again).
+constexpr int64_t kMaxWorkgroups = UINT32_MAX / (kDirsPerTile * kWaveSize);
+constexpr int kRootThreads = 256;
+constexpr int kRootBlock = 4 * kRootThreads;
+constexpr int kRootMaxRows = 65535;
+inline void root_grid(int M, int stride, unsigned *grid_x, unsigned *grid_y)
+{
+    *grid_x = (unsigned)(stride / kRootBlock) + (stride % kRootBlock != 0);
+    *grid_y = (unsigned)(M < kRootMaxRows ? M : kRootMaxRows);
+}
+
 // Envelope chunk walk: the chunk of samples [tc, tc + kChunk) (tc a multiple
 // of 32) yields the envelope outputs [tc - env_lead(H), ... + kChunk), where
 // env_lead(H) is H rounded up to a multiple of 32, so every output block

@@ -248,26 +248,26 @@ constexpr bool kStagesRoots = N >= 2 && !LINEAR;
 
 // Root plane: row i holds (signed_root(x), x) of channel i's samples at
 // [pad0, pad0 + T) and zero pairs elsewhere in its `stride` elements. A
-// workgroup takes kRootBlock elements of one row.
-constexpr int kRootThreads = 256;
-constexpr int kRootBlock = 4 * kRootThreads;
+// workgroup takes kRootBlock elements of row blockIdx.y and of every
+// gridDim.y-th after it.
 template <int N, int DT>
 __global__ void __launch_bounds__(kRootThreads)
-root_plane_kernel(const void *__restrict__ x, float2 *__restrict__ plane, int T, int pad0, int stride, int blocks)
+root_plane_kernel(const void *__restrict__ x, float2 *__restrict__ plane, int M, int T, int pad0, int stride)
 {
-    const int mic = blockIdx.x / blocks;
-    const int e0 = (blockIdx.x - mic * blocks) * kRootBlock + threadIdx.x;
-    const size_t chan = (size_t)mic * (size_t)T, row = (size_t)mic * (size_t)stride;
-    float v[4];
+    const int e0 = blockIdx.x * kRootBlock + threadIdx.x;
+    for (int mic = blockIdx.y; mic < M; mic += gridDim.y) {
+        const size_t chan = (size_t)mic * (size_t)T, row = (size_t)mic * (size_t)stride;
+        float v[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int t = e0 + j * kRootThreads - pad0;
-        v[j] = t >= 0 && t < T ? load_sample<DT>(x, chan + (size_t)t) : 0.0f;
-    }
+        for (int j = 0; j < 4; ++j) {
+            const int t = e0 + j * kRootThreads - pad0;
+            v[j] = t >= 0 && t < T ? load_sample<DT>(x, chan + (size_t)t) : 0.0f;
+        }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = e0 + j * kRootThreads;
-        if (e < stride) plane[row + (size_t)e] = make_float2(signed_root<N, true>(v[j]), v[j]);
+        for (int j = 0; j < 4; ++j) {
+            const int e = e0 + j * kRootThreads;
+            if (e < stride) plane[row + (size_t)e] = make_float2(signed_root<N, true>(v[j]), v[j]);
+        }
     }
 }
 

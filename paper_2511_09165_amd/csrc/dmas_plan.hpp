@@ -4,10 +4,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstddef>
 #include <cstdint>
 
+#include "dmas.h"
 #include "dmas_internal.hpp"
 
 namespace dmas {
@@ -72,6 +74,25 @@ inline size_t padded_plane_bytes(const dmas_plan_s *plan)
 {
     return plan->roots ? (size_t)plan->M * ((size_t)plan->pad0 + (size_t)plan->T + (size_t)plan->pad1) * sizeof(float2)
                        : 0;
+}
+
+// Output samples per workgroup without an envelope: segments share nothing, so
+// a cut costs only the workgroup's setup. One to three chunks, so that each of
+// `slots` places gets four workgroups where the record allows; more where the
+// launch would not hold the workgroups (kMaxWorkgroups: with three chunks,
+// images of 5e10 pixels and up). fixed > 0: that many, rounded up to 32.
+inline void choose_rf_segments(int T, int num_tiles, int64_t slots, int fixed, int *seg, int *nseg)
+{
+    int s = (fixed + 31) & ~31;
+    if (fixed <= 0) {
+        const int64_t all = ((int64_t)T + kChunk - 1) / kChunk;
+        int64_t chunks = 3;
+        while (chunks > 1 && (int64_t)num_tiles * ((T + chunks * kChunk - 1) / (chunks * kChunk)) < 4 * slots) --chunks;
+        const int64_t most = std::max<int64_t>(kMaxWorkgroups / num_tiles, 1);   // segments a tile
+        s = (int)(std::max(chunks, (all + most - 1) / most) * kChunk);
+    }
+    *seg = s;
+    *nseg = (T + s - 1) / s;
 }
 
 // Fill the root plane of input d_x (plans with roots only).

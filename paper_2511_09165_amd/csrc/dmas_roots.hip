@@ -11,10 +11,11 @@ hipError_t launch_roots_n(int dtype, const void *x, float2 *plane, int M, int T,
                           hipStream_t stream)
 {
     const int stride = pad0 + T + pad1;
-    const int blocks = (stride + kRootBlock - 1) / kRootBlock;
-    const dim3 grid((unsigned)M * (unsigned)blocks), threads(kRootThreads);
+    unsigned gx = 0, gy = 0;
+    root_grid(M, stride, &gx, &gy);
+    const dim3 grid(gx, gy), threads(kRootThreads);
     auto kern = dtype == 0 ? root_plane_kernel<N, 0> : dtype == 1 ? root_plane_kernel<N, 1> : root_plane_kernel<N, 2>;
-    hipLaunchKernelGGL(kern, grid, threads, 0, stream, x, plane, T, pad0, stride, blocks);
+    hipLaunchKernelGGL(kern, grid, threads, 0, stream, x, plane, M, T, pad0, stride);
     return hipGetLastError();
 }
 

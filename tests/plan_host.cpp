@@ -1,0 +1,64 @@
+// Host checks of how a plan sizes its launches, on the CPU: the RF segments
+// (choose_rf_segments) and the root pass's grid (root_grid) over sizes up to
+// the limits of the entry points. Prints "ok <checks>".
+#include "../paper_2511_09165_amd/csrc/dmas_plan.hpp"
+
+#include <cstdio>
+#include <cstdlib>
+
+static long checks = 0;
+#define CHECK(cond, ...)                              \
+    do {                                              \
+        ++checks;                                     \
+        if (!(cond)) {                                \
+            std::fprintf(stderr, "%s: ", #cond);      \
+            std::fprintf(stderr, __VA_ARGS__);        \
+            std::fprintf(stderr, "\n");               \
+            std::exit(1);                             \
+        }                                             \
+    } while (0)
+
+constexpr int64_t kThreads32 = (int64_t)1 << 32;   // a launch holds fewer in each dimension
+
+static void rf_segments()
+{
+    const int wg = dmas::kDirsPerTile * dmas::kWaveSize;
+    for (int64_t tiles : {1, 7, 523, 4096, 65537, 1 << 20, 4194304, 8388607}) {
+        for (int64_t T : {1, 256, 257, 769, 4096, 65536, 1 << 20, 1073739000}) {
+            for (int64_t slots : {256, 768, 1024, 2048}) {
+                int seg = 0, nseg = 0;
+                dmas::choose_rf_segments((int)T, (int)tiles, slots, 0, &seg, &nseg);
+                CHECK(seg > 0 && seg % 32 == 0, "tiles %ld T %ld seg %d", (long)tiles, (long)T, seg);
+                CHECK((int64_t)seg * nseg >= T && (int64_t)seg * (nseg - 1) < T, "tiles %ld T %ld", (long)tiles, (long)T);
+                CHECK(tiles * nseg * wg < kThreads32, "tiles %ld T %ld nseg %d", (long)tiles, (long)T, nseg);
+                // three chunks at most where the launch holds them
+                const int64_t three = (T + 3 * dmas::kChunk - 1) / (3 * dmas::kChunk);
+                if (tiles * three * wg < kThreads32) CHECK(seg <= 3 * dmas::kChunk, "tiles %ld T %ld", (long)tiles, (long)T);
+            }
+        }
+    }
+    int seg = 0, nseg = 0;
+    dmas::choose_rf_segments(1000, 5, 768, 100, &seg, &nseg);
+    CHECK(seg == 128 && nseg == 8, "fixed segments %d x %d", seg, nseg);
+}
+
+static void root_pass()
+{
+    for (int64_t M : {1, 8, 1024, 65535, 65536, 70000, 16777216, 1 << 30}) {
+        for (int64_t stride : {1, 1023, 1024, 1025, 16384, 1 << 24, 1700000000}) {
+            unsigned gx = 0, gy = 0;
+            dmas::root_grid((int)M, (int)stride, &gx, &gy);
+            CHECK((int64_t)gx * dmas::kRootThreads < kThreads32 && gy >= 1 && gy <= 65535, "M %ld stride %ld", (long)M, (long)stride);
+            CHECK((int64_t)gx * dmas::kRootBlock >= stride && ((int64_t)gx - 1) * dmas::kRootBlock < stride,
+                  "M %ld stride %ld", (long)M, (long)stride);
+        }
+    }
+}
+
+int main()
+{
+    rf_segments();
+    root_pass();
+    std::printf("ok %ld\n", checks);
+    return 0;
+}

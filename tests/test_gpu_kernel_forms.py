@@ -212,3 +212,17 @@ def test_fetch_moves_whole_results(D, T):
                 np.testing.assert_array_equal(y, ref)
         for t in tickets:
             srv.release(t)
+
+
+def test_root_plane_of_more_rows_than_a_grid_dimension(monkeypatch):
+    """More microphones than the root pass has workgroup rows: the bits of roots taken while
+    staging, and T1."""
+    f = synth.random_frame(np.random.default_rng(17), 70001, 9, 40, 2)
+    _say("root plane of 70001 rows")
+    got = {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        got[direct] = _image(f, f.x_f32())
+    np.testing.assert_array_equal(got["0"], got["1"])
+    taps = oracle.lowpass_taps(63, 5000.0, f.fs).astype(np.float32).astype(np.float64)
+    check_t1(got["0"], oracle.envelope(oracle.frame_rows(f, x=f.x_f32().astype(np.float64)), taps))
