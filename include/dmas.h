@@ -364,7 +364,9 @@ dmas_status_t dmas_server_release(dmas_server_t srv, uint64_t ticket);
 
 /* Copy a done frame's result into host memory h_out (synchronous): D x T FP32,
  * or D x ceil(T/k) for an envelope of a plan with env_decimation k; h_out
- * must hold that many floats. */
+ * must hold that many floats. Pinned memory is written by the DMA itself;
+ * results of 2 MiB and more in pageable memory by four host threads from pinned
+ * buffers (servers without resident workers). */
 dmas_status_t dmas_server_fetch(dmas_server_t srv, uint64_t ticket, float *h_out);
 
 /* Move up to max records of auto-released, completed frames into out

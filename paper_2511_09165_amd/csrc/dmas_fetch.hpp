@@ -1,13 +1,17 @@
-// Copies of device results into a caller's pageable host memory: chunks go by
-// DMA into pinned buffers and from there to the destination, on several host
-// threads, so that the DMA, the copies and the destination's page faults
-// overlap. Twelve results of 53 MB in all, on warm and on fresh memory: one
-// thread's hipMemcpy 15 and 5-13 GB/s, four threads with 1 MiB chunks and a
-// stream each 28 and 10-24 GB/s (six or eight threads, 512 KiB or 2 MiB chunks
-// and one stream for all measured the same or slower). Each thread maps its
-// chunk's pages while the chunk's DMA is under way: with a fresh array per
-// result, whose page faults cost more than the copies, the twelve results with
-// their kernels take 4.2 instead of 6.0 ms (2.8 on pages already mapped).
+// Copies of device results into a caller's memory.
+//
+// Memory that HIP knows (pinned, registered, managed) takes one hipMemcpy: for
+// pinned memory one DMA, 56.6 GB/s for a result of 53 MB (41 in the chunks
+// below).
+//
+// Pageable memory: chunks go by DMA into pinned buffers and from there to the
+// destination, on several host threads, so that the DMA, the copies and the
+// destination's page faults overlap. A result of 53 MB into mapped and into
+// fresh pages: hipMemcpy 18 and 10 GB/s, four threads with 1 MiB chunks and a
+// stream each 40-46 and 35-37 (six or eight threads, 512 KiB or 2 MiB chunks and
+// one stream for all measured the same or slower). Each thread maps its chunk's
+// pages while the chunk's DMA is under way, since a fresh array's page faults
+// cost more than the copies.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,7 +51,10 @@ public:
             }
         }
         ready_ = e == hipSuccess;
-        if (!ready_) shut();
+        if (!ready_) {
+            shut();
+            (void)hipGetLastError();   // not the caller's
+        }
         return e;
     }
 
@@ -59,7 +66,7 @@ public:
     hipError_t copy(void *dst, const void *src, size_t bytes)
     {
         std::unique_lock<std::mutex> turn(turn_, std::try_to_lock);
-        if (!ready_ || bytes < 2 * kChunk || !turn.owns_lock())
+        if (!ready_ || bytes < 2 * kChunk || !turn.owns_lock() || !pageable(dst))
             return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
         {
             std::lock_guard<std::mutex> lk(mu_);
@@ -80,6 +87,15 @@ public:
     }
 
 private:
+    // Whether HIP knows nothing of the memory at p.
+    static bool pageable(const void *p)
+    {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
+        (void)hipGetLastError();   // some versions report such memory as an error
+        return true;
+    }
+
     // Moves chunks of the open job until none is left, through buffer i.
     void work(int i)
     {
