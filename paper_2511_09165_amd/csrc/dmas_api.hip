@@ -742,13 +742,17 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     // global-to-LDS loads). With Kahan or FP64 sums, whose register budgets
     // differ, the per-microphone reads one ahead stay (1.4-2.4 % faster
     // there). DMAS_BLOCK_TABLES=0/1 overrides the choice for M <= 64 (tuning).
+    // Single calls that take the roots while staging read per-block tables
+    // whatever the other launches of the plan (a server's) read.
     p->direct = p->roots && p->tables && direct_roots_pay(p);
     if (const char *dr = std::getenv("DMAS_DIRECT_ROOTS")) p->direct = p->roots && p->tables && std::atoi(dr) != 0;
-    p->block_tables = M > dmas::kWaveSize || p->compensated == DMAS_ACCUM_F32 || p->direct;
-    if (const char *bt = std::getenv("DMAS_BLOCK_TABLES"))
+    p->block_tables = M > dmas::kWaveSize || p->compensated == DMAS_ACCUM_F32;
+    if (const char *bt = std::getenv("DMAS_BLOCK_TABLES")) {
         p->block_tables = M > dmas::kWaveSize || std::atoi(bt) != 0;
+        p->direct = p->direct && p->block_tables;
+    }
     p->block_tables = p->block_tables && p->tables;
-    p->direct = p->direct && p->block_tables && !std::getenv("DMAS_RING_SHARING");
+    p->direct = p->direct && !std::getenv("DMAS_RING_SHARING");
     const int C = dmas::kChunk;
     const int H = (L - 1) / 2;
     // Window length. With tables a microphone's window starts at the smallest
@@ -873,6 +877,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         return fail(DMAS_ERR_DEVICE, "internal: LDS layout mismatch");
     }
 
+    p->direct_block = dmas::direct_block_of(mb, M, dmas::table_block_max(n));
     if (p->direct && std::max(dmas::direct_shape_of(p, true).lds_bytes, dmas::direct_shape_of(p, false).lds_bytes) > lds_cap)
         p->direct = false;
 
@@ -934,9 +939,11 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     if (std::getenv("DMAS_LOG"))
         fprintf(stderr,
                 "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d range=%d row=%d mb=%d seg=%d/%d nseg=%d/%d lds=%zu/%zu "
-                "occupancy=%d/%d\n",
+                "occupancy=%d/%d tables=%s direct=%d\n",
                 M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_rf, p->seg_env, p->nseg_rf,
-                p->nseg_env, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env);
+                p->nseg_env, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env,
+                !p->tables ? "none" : !p->block_tables ? "mics" : p->share_rings ? "blocks,shared" : "blocks",
+                p->direct ? p->direct_block : 0);
     *out = p;
     return DMAS_OK;
 }

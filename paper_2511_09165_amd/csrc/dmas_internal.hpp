@@ -30,7 +30,7 @@ struct KernelParams {
     const int32_t *tile_dirs; // num_tiles x dirs_per_tile direction indices (-1 = empty), device
     const int32_t *tile_off;  // optional, num_tiles x dirs_per_tile x M: LDS element where
                               // each direction's window of each microphone starts,
-                              // (mic % mic_block) * row + (delay - the window's start)
+                              // (mic % table_block) * row + (delay - the window's start)
     const int32_t *tile_dref; // optional, num_tiles x M: the delays the windows start at
     const float *taps;        // fir_len envelope taps, device
     int32_t M, T, D;
@@ -42,6 +42,9 @@ struct KernelParams {
                               // |delay - reference delay| within a tile; 0 with tables
     int32_t row;              // LDS row length per microphone (floats)
     int32_t mic_block;        // microphones per LDS block, <= kMaxMicBlock
+    int32_t table_block;      // the block that tile_off was built for: mic_block, but with
+                              // kDelayTableDirect and Kahan or FP64 sums also a multiple of
+                              // it or at least M
     int32_t dtype;            // dmas_dtype_t
     int32_t ng_fp64;          // evaluate Newton-Girard in FP64
     double fs, c;
@@ -75,16 +78,15 @@ struct LaunchShape {
 // tables (whole samples). With kDelayTable the hot loop reads each
 // microphone's offset through the scalar cache one ahead of use; with
 // kDelayTableBlocks each wave reads its block's offsets and the reference
-// delays of the rows it stages as scalars before the block's barrier, and the
+// delays of the rows it stages as scalars, under the window copies, and the
 // block's microphone loop is straight-line code (per-microphone scalar reads
 // of a large table left their latency in the hot loop). The plan picks the
-// block form for more than 64 microphones and for plain FP32 sums up to
-// order 7.
+// block form for more than 64 microphones and for plain FP32 sums.
 // kDelayTableBlocksShared is kDelayTableBlocks with the envelope rings in the
 // window region (below), which the plan picks when it raises the occupancy.
 // kDelayTableDirect is kDelayTableBlocks with the roots taken from the
-// channels while staging: single calls of small frames, n >= 2. A mode of its
-// own, because the staging code raised the other kernels' SGPRs past the
+// channels while staging: single calls of small frames, n >= 2, whichever form
+// the plan's other launches take. A mode of its own, because the staging code raised the other kernels' SGPRs past the
 // budget of eight waves per SIMD.
 enum : int { kDelayComputed = 0, kDelayLinear = 1, kDelayTable = 2, kDelayTableBlocks = 3, kDelayTableBlocksShared = 4,
              kDelayTableDirect = 5 };

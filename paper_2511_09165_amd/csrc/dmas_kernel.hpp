@@ -623,6 +623,9 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
     constexpr bool LINEAR = DM == kDelayLinear;
     constexpr bool TAB = DM == kDelayTable;          // tables through the scalar cache
     constexpr bool TAB_BLOCKS = block_tables(DM); // offsets and references per block, as scalars
+    // blocks may be smaller than those the offsets were built for: plans with
+    // Kahan or FP64 sums, whose other launches read the tables per microphone
+    constexpr bool SHIFT = takes_roots(DM) && ACC != kAccF32;
     constexpr int W = kDirsPerTile;
     constexpr int K = kSamplesPerLane;
     constexpr int C = kChunk;
@@ -911,6 +914,7 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
         const bool compute = ch < nchunks;
         Acc<N, CF, ACC> acc_pass[K];
         auto &acc = *(PEEL ? &acc_pass : &acc_kept);
+        int trow = 0;   // SHIFT: the block's first row in the tables' block
 
         for (int blk = 0; blk < (compute ? nblocks : 0); ++blk) {
             if (!all_mics) block_geometry(blk);
@@ -969,11 +973,12 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
             // ---- hot loop: delayed samples -> roots -> power sums ----
             if (active) {
                 const int nm = min(p.mic_block, p.M - blk * p.mic_block);
+                const int shift = SHIFT ? trow * p.row : 0;
                 // microphone i of the block: its window starts at LDS element off;
                 // the chunk's first microphone starts the sums (no clearing)
                 auto mic_step = [&](auto first, int i, int off) {
                     constexpr bool FIRST = decltype(first)::value;
-                    const Elem *src = xwin + off + lane;
+                    const Elem *src = xwin + (off - shift) + lane;
                     if constexpr (ROOTS) {
                         float2 v[K];
 #pragma unroll
@@ -1053,6 +1058,10 @@ __device__ __forceinline__ void dmas_body(const KernelParams &p, const int tile,
                         for (int i = 0; i < nm; ++i) mic_step(rest_t{}, i, off_of(i));
                     }
                 }
+            }
+            if constexpr (SHIFT) {
+                trow += p.mic_block;
+                if (trow >= p.table_block) trow = 0;
             }
         }
 

@@ -43,6 +43,7 @@ struct dmas_plan_s {
     int halo = 0;          // largest |delay - reference direction's| within a tile
     int range = 0;         // largest range of a microphone's delays within a tile
     int mic_block = 0;
+    int direct_block = 0;  // microphones per LDS block of the launches without a root plane
     int row = 0;
     bool two_pass = false; // envelope calls: RF image into the output, then the filter over it in place
     int seg_rf = 0, seg_env = 0;
@@ -130,7 +131,7 @@ inline KernelParams make_params(const dmas_plan_s *plan, const void *d_x, const 
     kp.seg_len = env ? plan->seg_env : plan->seg_rf;
     kp.halo = plan->tables ? 0 : plan->halo;   // tables hold the window starts
     kp.row = plan->row;
-    kp.mic_block = plan->mic_block;
+    kp.mic_block = kp.table_block = plan->mic_block;
     kp.dtype = plan->dtype;
     kp.ng_fp64 = plan->ng_fp64;
     kp.fs = plan->fs;
@@ -166,8 +167,20 @@ inline LaunchShape direct_shape_of(const dmas_plan_s *p, bool env)
 {
     LaunchShape ls = shape_of(p, env);
     ls.delay = kDelayTableDirect;
-    ls.lds_bytes = (size_t)kernel_lds_bytes(p->mic_block, p->row, 2, env, (p->fir_len - 1) / 2, kDelayTableDirect);
+    ls.lds_bytes = (size_t)kernel_lds_bytes(p->direct_block, p->row, 2, env, (p->fir_len - 1) / 2, kDelayTableDirect);
     return ls;
+}
+
+// Its block, at most cap microphones, on tables built for blocks of mic_block:
+// the whole array's rows lie one after another (mic_block >= M), or whole blocks
+// make up one of the tables'.
+inline int direct_block_of(int mic_block, int M, int cap)
+{
+    if (mic_block <= cap) return mic_block;
+    if (mic_block >= M) return cap;
+    int b = cap;
+    while (mic_block % b) --b;
+    return b;
 }
 
 // Workgroups of one launch of the plan.
@@ -189,7 +202,8 @@ inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const f
                                float *d_out, float in_scale, bool env, hipStream_t stream)
 {
     const bool fused = env && !plan->two_pass;
-    const KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused, padded);
+    KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused, padded);
+    if (plan->direct) kp.mic_block = plan->direct_block;
     hipError_t e = launch_plan(plan->order, &kp, plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused),
                                stream);
     if (e == hipSuccess && env && !fused)

@@ -1,6 +1,7 @@
 // Host checks of how a plan sizes its launches, on the CPU: the RF segments
 // (choose_rf_segments) and the root pass's grid (root_grid) over sizes up to
-// the limits of the entry points. Prints "ok <checks>".
+// the limits of the entry points, and the blocks of launches without a root
+// plane (direct_block_of) against the tables'. Prints "ok <checks>".
 #include "../paper_2511_09165_amd/csrc/dmas_plan.hpp"
 
 #include <cstdio>
@@ -55,9 +56,32 @@ static void root_pass()
     }
 }
 
+// A plane-free launch walks blocks of b microphones over tables built for
+// blocks of mb: with the row the kernel keeps (zero at the first block, b more
+// at each, zero again at mb), microphone i's row is that of the tables.
+static void direct_blocks()
+{
+    for (int M = 1; M <= 80; ++M) {
+        for (int mb = 1; mb <= M; ++mb) {
+            for (int cap : {4, 16}) {
+                const int b = dmas::direct_block_of(mb, M, cap);
+                CHECK(b >= 1 && b <= cap && b <= mb, "M %d mb %d cap %d", M, mb, cap);
+                int trow = 0;
+                for (int m0 = 0; m0 < M; m0 += b) {
+                    for (int i = m0; i < m0 + b && i < M; ++i)
+                        CHECK(i % mb - trow == i - m0, "M %d mb %d b %d microphone %d", M, mb, b, i);
+                    trow += b;
+                    if (trow >= mb) trow = 0;
+                }
+            }
+        }
+    }
+}
+
 int main()
 {
     rf_segments();
+    direct_blocks();
     root_pass();
     std::printf("ok %ld\n", checks);
     return 0;

@@ -1,0 +1,59 @@
+"""Which forms a plan's launches take, read from the line that DMAS_LOG prints."""
+
+import re
+
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(f"[gpu] {msg}", flush=True)
+
+
+def _logged(capfd, monkeypatch, f, **kw):
+    """A plan for frame f and what its DMAS_LOG line says, as a dict of strings."""
+    from paper_2511_09165_amd import plan_for_frame
+    monkeypatch.setenv("DMAS_LOG", "1")
+    capfd.readouterr()
+    plan = plan_for_frame(f, **kw)
+    lines = [ln for ln in capfd.readouterr().err.splitlines() if ln.startswith("[dmas] plan ")]
+    assert len(lines) == 1
+    return plan, dict(re.findall(r"(\w+)=(\S+)", lines[0]))
+
+
+# the block of the tables (None: the plan's) and of the plane-free launch: the whole array, a
+# multiple of it, a divisor of it, one that no smaller block divides
+@pytest.mark.parametrize("M,block", [(9, None), (33, None), (64, None), (40, 24), (40, 20), (37, 23)])
+@pytest.mark.parametrize("accumulate", ["kahan", "f64"])
+def test_plane_free_calls_leave_the_other_launches_as_they_are(M, block, accumulate, monkeypatch, capfd):
+    """Kahan and FP64 sums: whether single calls take the roots while staging does not change the
+    tables, blocks and LDS of the plan's other launches (a server's); single calls and served
+    frames give the bits of a plan that reads a root plane."""
+    from paper_2511_09165_amd import Server
+    f = synth.random_frame(np.random.default_rng(M), M, 21, 900, 3)
+    x = f.x_f32()
+    if block is not None:
+        monkeypatch.setenv("DMAS_MIC_BLOCK", str(block))
+    got, log = {}, {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        plan, log[direct] = _logged(capfd, monkeypatch, f, accumulate=accumulate)
+        _say(f"M={M} block={block} {accumulate} direct={log[direct].get('direct')}")
+        with plan, Server(64 << 20, staging=4 << 20) as srv:
+            xt = torch.from_numpy(x).cuda()
+            t = srv.submit(plan, x)
+            srv.wait(t, 30.0)
+            got[direct] = [plan.envelope(xt).cpu().numpy(), plan.beamform(xt).cpu().numpy(), srv.fetch(t)]
+            srv.release(t)
+    same = ("tables", "mb", "row", "lds", "occupancy", "seg", "nseg")
+    assert {k: log["1"].get(k) for k in same} == {k: log["0"].get(k) for k in same}
+    assert log["0"]["direct"] == "0" and 1 <= int(log["1"]["direct"]) <= 16
+    assert log["1"]["tables"] == "mics"
+    for a, b in zip(got["0"], got["1"]):
+        np.testing.assert_array_equal(a, b)
+    np.testing.assert_array_equal(got["1"][2], got["1"][0])
