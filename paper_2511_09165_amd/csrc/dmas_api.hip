@@ -262,28 +262,6 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
     }
 }
 
-// Zero pairs around the rows of single calls' root planes, so that windows
-// reaching past the record's ends are copied like all others instead of
-// element by element, which took several times as long: workgroups at the ends
-// outlasted the rest (517 microphones, 361 x 4096 at order 2: 157 us against
-// 100 us each, and the launch lasted as long as they did). A delay is at most
-// the microphone's distance from the origin in samples (the triangle
-// inequality, near and far field); a window starts at most that and the halo
-// before sample 0 and ends at most that, a chunk and the halo after T. Rows
-// that would more than double (plus 1024 samples) stay unpadded.
-void plane_pads(const dmas_plan_desc_t *d, double c, int chunk, dmas_plan_s *p)
-{
-    double r2 = 0;
-    for (int i = 0; i < d->num_mics; ++i) {
-        const double *r = d->mic_pos + 3 * (size_t)i;
-        r2 = std::max(r2, r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-    }
-    const double reach = std::ceil(d->fs * std::sqrt(r2) / c * (1.0 + 1e-5)) + 2.0 + p->halo;
-    if (2.0 * reach + chunk + 4 > (double)p->T + 1024) return;
-    p->pad0 = ((int)reach + 3) & ~3;
-    p->pad1 = ((int)reach + chunk + 4 + 3) & ~3;
-}
-
 // Whether a single call takes the roots while staging instead of reading them
 // from a root plane (the same bits). The plane costs a launch (2-3 us) and a pool
 // allocation and free around the call (about 15 us of host time, which bounds
@@ -536,6 +514,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
                     cur);
     hipStream_t st = static_cast<hipStream_t>(stream);
     float2 *plane = nullptr;
+    bool padded = false;
     hipError_t e = hipSuccess;
     if (plan->roots && noalloc) {
         const size_t need = dmas::plane_bytes(plan);
@@ -545,7 +524,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
                         "dmas_envelope_noalloc",
                         need, plan->M, plan->T, (size_t)DMAS_NOALLOC_SCRATCH_BYTES);
         float2 *fixed = nullptr;
-        const bool padded = dmas::padded_plane_bytes(plan) <= DMAS_NOALLOC_SCRATCH_BYTES;
+        padded = dmas::padded_plane_bytes(plan) <= DMAS_NOALLOC_SCRATCH_BYTES;
         if (!plan->direct) {
             e = scratch_address(plan->device, &fixed);
             if (e != hipSuccess) return hip_fail(e, "address of the fixed root-plane scratch");
@@ -564,15 +543,16 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
         hipMemPool_t pool = nullptr;
         e = device_pool(plan->device, &pool);
         if (e != hipSuccess) return hip_fail(e, "root-plane memory pool");
+        padded = true;
         e = hipMallocFromPoolAsync(reinterpret_cast<void **>(&plane), dmas::padded_plane_bytes(plan), pool, st);
         if (e != hipSuccess) return hip_fail(e, "root-plane allocation");
-        e = dmas::stage_roots(plan, d_x, plane, true, st);
+        e = dmas::stage_roots(plan, d_x, plane, padded, st);
         if (e != hipSuccess) {
             (void)hipFreeAsync(plane, st);
             return hip_fail(e, "root-plane launch");
         }
     }
-    e = dmas::launch_image(plan, d_x, plane, true, d_out, in_scale, env, st);
+    e = dmas::launch_image(plan, d_x, plane, padded, d_out, in_scale, env, st);
     if (plane) {
         const hipError_t ef = hipFreeAsync(plane, st);
         if (e == hipSuccess) e = ef;
@@ -881,7 +861,14 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     if (p->direct && std::max(dmas::direct_shape_of(p, true).lds_bytes, dmas::direct_shape_of(p, false).lds_bytes) > lds_cap)
         p->direct = false;
 
-    if (p->roots) plane_pads(d, c, C, p);
+    if (p->roots) {
+        double r2 = 0;   // a delay is at most the microphone's distance from the origin (triangle inequality)
+        for (int i = 0; i < M; ++i) {
+            const double *r = d->mic_pos + 3 * (size_t)i;
+            r2 = std::max(r2, r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+        }
+        dmas::plane_pads(p, d->fs * std::sqrt(r2) / c);
+    }
 
     // Build the delay tables: the kernel reads window offsets and reference
     // delays instead of evaluating eq. (1) on the device and moving the
@@ -939,11 +926,11 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     if (std::getenv("DMAS_LOG"))
         fprintf(stderr,
                 "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d range=%d row=%d mb=%d seg=%d/%d nseg=%d/%d lds=%zu/%zu "
-                "occupancy=%d/%d tables=%s direct=%d\n",
+                "occupancy=%d/%d tables=%s direct=%d pads=%d/%d\n",
                 M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_rf, p->seg_env, p->nseg_rf,
                 p->nseg_env, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env,
                 !p->tables ? "none" : !p->block_tables ? "mics" : p->share_rings ? "blocks,shared" : "blocks",
-                p->direct ? p->direct_block : 0);
+                p->direct ? p->direct_block : 0, p->pad0, p->pad1);
     *out = p;
     return DMAS_OK;
 }

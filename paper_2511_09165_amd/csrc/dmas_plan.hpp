@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -75,6 +76,26 @@ inline size_t padded_plane_bytes(const dmas_plan_s *plan)
 {
     return plan->roots ? (size_t)plan->M * ((size_t)plan->pad0 + (size_t)plan->T + (size_t)plan->pad1) * sizeof(float2)
                        : 0;
+}
+
+// Zero pairs around the rows of single calls' root planes, so that windows
+// reaching past the record's ends are copied like all others instead of
+// element by element, which took several times as long: workgroups at the ends
+// outlasted the rest (517 microphones, 361 x 4096 at order 2: 157 us against
+// 100 us each, and the launch lasted as long as they did). A chunk starts at a
+// sample of [0, T), its windows at most max_delay (samples, either way) and,
+// without tables, the halo before it; the copy is `row` pairs long. Rows that
+// would more than double (plus 1024 samples) stay unpadded.
+inline void plane_pads(dmas_plan_s *plan, double max_delay)
+{
+    const double reach = std::ceil(max_delay * (1.0 + 1e-5)) + 2.0;
+    const int halo = plan->tables ? 0 : plan->halo;
+    const double before = reach + halo, after = std::max(0.0, reach - halo + plan->row);
+    plan->pad0 = plan->pad1 = 0;
+    if (before + after + 6 > (double)plan->T + 1024) return;
+    const int pad0 = ((int)before + 3) & ~3, pad1 = ((int)after + 3) & ~3;
+    plan->pad0 = pad0;
+    plan->pad1 = pad1;
 }
 
 // Output samples per workgroup without an envelope: segments share nothing, so

@@ -1,7 +1,8 @@
 // Host checks of how a plan sizes its launches, on the CPU: the RF segments
 // (choose_rf_segments) and the root pass's grid (root_grid) over sizes up to
 // the limits of the entry points, and the blocks of launches without a root
-// plane (direct_block_of) against the tables'. Prints "ok <checks>".
+// plane (direct_block_of) against the tables', and the padding of
+// root planes (plane_pads). Prints "ok <checks>".
 #include "../paper_2511_09165_amd/csrc/dmas_plan.hpp"
 
 #include <cstdio>
@@ -78,8 +79,51 @@ static void direct_blocks()
     }
 }
 
+// Padded rows hold every window of a plan: a chunk starts in [0, T), a window
+// at its microphone's smallest delay in the tile (tables) or at the reference
+// delay less the halo, and is `row` pairs long.
+static void plane_padding()
+{
+    int padded = 0, plain = 0;
+    for (bool tables : {true, false}) {
+        for (double delay : {0.0, 0.4, 13.7, 105.5, 105.49951, 700.0, 5000.0, 9.9e7}) {
+            for (int halo : {0, 1, 29, 62, 400}) {
+                for (int range : {halo, halo + halo / 4, 2 * halo}) {
+                    for (int T : {1, 255, 300, 2048, 8192, 100000, 1073739000}) {
+                        for (int M : {1, 64, 1024, 20000000}) {
+                            dmas_plan_s p;
+                            p.tables = tables;
+                            p.roots = true;
+                            p.halo = halo;
+                            p.range = range;
+                            p.M = M;
+                            p.T = T;
+                            p.row = (dmas::kChunk + (tables ? range : 2 * halo) + 3) & ~3;
+                            dmas::plane_pads(&p, delay);
+                            CHECK(p.pad0 >= 0 && p.pad1 >= 0 && p.pad0 % 4 == 0 && p.pad1 % 4 == 0, "T %d", T);
+                            CHECK((int64_t)p.pad0 + T + p.pad1 <= INT32_MAX && p.pad0 + p.pad1 <= T + 1024, "T %d", T);
+                            if (!p.pad1) {
+                                ++plain;
+                                continue;
+                            }
+                            ++padded;
+                            const int d = (int)std::ceil(delay) + 1;        // delays lie in [-d, d]
+                            const int first = 0 - d - (tables ? 0 : halo);
+                            const int last = T - 1 + d - (tables ? 0 : halo) + p.row;
+                            CHECK(first >= -p.pad0 && last <= T + p.pad1, "delay %g halo %d range %d T %d: [%d, T%+d) in [%d, T%+d)",
+                                  delay, halo, range, T, first, last - T, -p.pad0, p.pad1);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    CHECK(padded > 100 && plain > 100, "%d padded, %d plain", padded, plain);
+}
+
 int main()
 {
+    plane_padding();
     rf_segments();
     direct_blocks();
     root_pass();
