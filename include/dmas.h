@@ -186,9 +186,10 @@ dmas_status_t dmas_plan_query(dmas_plan_t plan, dmas_plan_info_t *info);
  * plane of M x T (root, sample) FP32 pairs, which the beamformer then reads
  * in place of d_x; the plane is allocated and freed in stream order from a
  * device memory pool that the library keeps per device (M*T*8 bytes per call
- * in flight, plus zeros around each row for the largest delay and a chunk), so
- * one plan may be used on several streams at once. Small frames take the same
- * roots inside the beamformer and use no plane. Errors:
+ * in flight, and where the device has room zeros around each row for the
+ * largest delay and a chunk, at most 256 MiB), so one plan may be used on
+ * several streams at once. Small frames take the same roots inside the
+ * beamformer and use no plane. Errors:
  * DMAS_ERR_INVALID_ARG (NULL pointers, in_scale, plan of another device),
  * DMAS_ERR_OUT_OF_MEMORY (plane allocation), DMAS_ERR_DEVICE (launch). */
 dmas_status_t dmas_beamform(dmas_plan_t plan, const void *d_x, float *d_y,

@@ -543,8 +543,8 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
         hipMemPool_t pool = nullptr;
         e = device_pool(plan->device, &pool);
         if (e != hipSuccess) return hip_fail(e, "root-plane memory pool");
-        padded = true;
-        e = hipMallocFromPoolAsync(reinterpret_cast<void **>(&plane), dmas::padded_plane_bytes(plan), pool, st);
+        auto alloc = [&](void **mem, size_t bytes) { return hipMallocFromPoolAsync(mem, bytes, pool, st); };
+        e = dmas::allocate_plane(plan, alloc, &plane, &padded);
         if (e != hipSuccess) return hip_fail(e, "root-plane allocation");
         e = dmas::stage_roots(plan, d_x, plane, padded, st);
         if (e != hipSuccess) {

@@ -277,7 +277,7 @@ root_plane_kernel(const void *__restrict__ x, float2 *__restrict__ plane, int M,
 // inside it is copied by global-to-LDS loads, which complete in the background
 // (the wave's vmcnt): the caller waits for them before the barrier that
 // publishes the windows. Planes of single calls are padded so that every
-// window is, where that costs little (plane_pads). (Against loading into registers and writing those to
+// window is, where that costs little memory (plane_pads). (Against loading into registers and writing those to
 // LDS: 4.0-7.5 % faster across the kernels, bitwise the same.)
 __device__ __forceinline__ void stage_row_roots(float2 *__restrict__ dst, const float2 *__restrict__ plane, int base,
                                                 int row, int lo, int hi, int T, int lane)

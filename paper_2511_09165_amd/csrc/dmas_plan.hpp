@@ -85,7 +85,10 @@ inline size_t padded_plane_bytes(const dmas_plan_s *plan)
 // 100 us each, and the launch lasted as long as they did). A chunk starts at a
 // sample of [0, T), its windows at most max_delay (samples, either way) and,
 // without tables, the halo before it; the copy is `row` pairs long. Rows that
-// would more than double (plus 1024 samples) stay unpadded.
+// would more than double (plus 1024 samples) stay unpadded, and so do planes
+// that the padding would make kMaxPadBytes longer (short records of very many
+// microphones: it would be most of their plane).
+constexpr int64_t kMaxPadBytes = (int64_t)256 << 20;
 inline void plane_pads(dmas_plan_s *plan, double max_delay)
 {
     const double reach = std::ceil(max_delay * (1.0 + 1e-5)) + 2.0;
@@ -94,8 +97,27 @@ inline void plane_pads(dmas_plan_s *plan, double max_delay)
     plan->pad0 = plan->pad1 = 0;
     if (before + after + 6 > (double)plan->T + 1024) return;
     const int pad0 = ((int)before + 3) & ~3, pad1 = ((int)after + 3) & ~3;
+    if ((int64_t)plan->M * (pad0 + pad1) * (int64_t)sizeof(float2) > kMaxPadBytes) return;
     plan->pad0 = pad0;
     plan->pad1 = pad1;
+}
+
+// Memory for a call's root plane from alloc(void **, bytes): with the rows
+// padded, or without where the device has no room for the padding.
+template <class Alloc>
+inline hipError_t allocate_plane(const dmas_plan_s *plan, Alloc &&alloc, float2 **plane, bool *padded)
+{
+    const size_t plain = plane_bytes(plan), full = padded_plane_bytes(plan);
+    void *mem = nullptr;
+    *padded = true;
+    hipError_t e = alloc(&mem, full);
+    if (e == hipErrorOutOfMemory && full > plain) {
+        (void)hipGetLastError();
+        *padded = false;
+        e = alloc(&mem, plain);
+    }
+    *plane = e == hipSuccess ? static_cast<float2 *>(mem) : nullptr;
+    return e;
 }
 
 // Output samples per workgroup without an envelope: segments share nothing, so

@@ -1,12 +1,20 @@
 // Host checks of how a plan sizes its launches, on the CPU: the RF segments
 // (choose_rf_segments) and the root pass's grid (root_grid) over sizes up to
 // the limits of the entry points, and the blocks of launches without a root
-// plane (direct_block_of) against the tables', and the padding of
-// root planes (plane_pads). Prints "ok <checks>".
+// plane (direct_block_of) against the tables', and the padding and
+// memory of root planes (plane_pads, allocate_plane). Prints "ok <checks>".
 #include "../paper_2511_09165_amd/csrc/dmas_plan.hpp"
 
 #include <cstdio>
 #include <cstdlib>
+
+static hipError_t g_error = hipSuccess;
+extern "C" hipError_t hipGetLastError(void)
+{
+    const hipError_t e = g_error;
+    g_error = hipSuccess;
+    return e;
+}
 
 static long checks = 0;
 #define CHECK(cond, ...)                              \
@@ -100,8 +108,10 @@ static void plane_padding()
                             p.T = T;
                             p.row = (dmas::kChunk + (tables ? range : 2 * halo) + 3) & ~3;
                             dmas::plane_pads(&p, delay);
+                            const size_t extra = dmas::padded_plane_bytes(&p) - dmas::plane_bytes(&p);
                             CHECK(p.pad0 >= 0 && p.pad1 >= 0 && p.pad0 % 4 == 0 && p.pad1 % 4 == 0, "T %d", T);
                             CHECK((int64_t)p.pad0 + T + p.pad1 <= INT32_MAX && p.pad0 + p.pad1 <= T + 1024, "T %d", T);
+                            CHECK(extra <= (size_t)256 << 20, "M %d T %d: %zu bytes of padding", M, T, extra);
                             if (!p.pad1) {
                                 ++plain;
                                 continue;
@@ -121,9 +131,45 @@ static void plane_padding()
     CHECK(padded > 100 && plain > 100, "%d padded, %d plain", padded, plain);
 }
 
+// Where the device has no room for the padding the plane goes without it.
+static void plane_memory()
+{
+    dmas_plan_s p;
+    p.roots = true;
+    p.M = 8;
+    p.T = 1000;
+    p.pad0 = 40;
+    p.pad1 = 300;
+    const size_t plain = 8 * 1000 * 8, full = 8 * 1340 * 8;
+    float2 *plane = nullptr;
+    bool padded = false;
+    for (size_t room : {full, full - 1, plain, plain - 1}) {
+        int calls = 0;
+        auto alloc = [&](void **mem, size_t bytes) {
+            ++calls;
+            if (bytes > room) {
+                g_error = hipErrorOutOfMemory;
+                return hipErrorOutOfMemory;
+            }
+            *mem = &p;
+            return hipSuccess;
+        };
+        g_error = hipSuccess;
+        const hipError_t e = dmas::allocate_plane(&p, alloc, &plane, &padded);
+        CHECK((e == hipSuccess) == (room >= plain), "room %zu", room);
+        CHECK((plane != nullptr) == (e == hipSuccess), "room %zu", room);
+        if (e == hipSuccess) CHECK(padded == (room >= full) && g_error == hipSuccess, "room %zu", room);
+        CHECK(calls == (room >= full ? 1 : 2), "room %zu: %d calls", room, calls);
+    }
+    int calls = 0;                                  // other errors are reported as they are
+    auto broken = [&](void **, size_t) { ++calls; return hipErrorInvalidValue; };
+    CHECK(dmas::allocate_plane(&p, broken, &plane, &padded) == hipErrorInvalidValue && calls == 1, "%d calls", calls);
+}
+
 int main()
 {
     plane_padding();
+    plane_memory();
     rf_segments();
     direct_blocks();
     root_pass();
