@@ -185,7 +185,6 @@ void plan_free(dmas_plan_s *p)
     (void)hipFree(p->d_dirs);
     (void)hipFree(p->d_tiles);
     (void)hipFree(p->d_tile_off);
-    (void)hipFree(p->d_tile_dref);
     (void)hipFree(p->d_taps);
     (void)hipFree(p->d_pulse);
     if (switched) (void)hipSetDevice(cur);
@@ -875,12 +874,13 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     // results between lanes.
     if (p->tables) {
         const size_t n_off = (size_t)p->num_tiles * W * M, n_dref = (size_t)p->num_tiles * M;
-        // kTableBlockMax spare entries: a scalar block read may run past the last row
-        e = hipMalloc((void **)&p->d_tile_off, sizeof(int32_t) * (n_off + dmas::kTableBlockMax));
-        if (e == hipSuccess) e = hipMemset(p->d_tile_off + n_off, 0, sizeof(int32_t) * dmas::kTableBlockMax);
-        if (e == hipSuccess) e = hipMalloc((void **)&p->d_tile_dref, sizeof(int32_t) * (n_dref + dmas::kTableBlockMax));
-        if (e == hipSuccess) e = hipMemset(p->d_tile_dref + n_dref, 0, sizeof(int32_t) * dmas::kTableBlockMax);
+        // one allocation, the reference delays behind the offsets, and behind them
+        // kTableBlockMax spare entries: scalar reads of a block of either may run past
+        // the last row (of the offsets: into the reference delays)
+        e = hipMalloc((void **)&p->d_tile_off, sizeof(int32_t) * (n_off + n_dref + dmas::kTableBlockMax));
+        if (e == hipSuccess) e = hipMemset(p->d_tile_off + n_off + n_dref, 0, sizeof(int32_t) * dmas::kTableBlockMax);
         if (e == hipSuccess) {
+            p->d_tile_dref = p->d_tile_off + n_off;
             auto kern = p->nearfield ? tile_table_kernel<true> : tile_table_kernel<false>;
             hipLaunchKernelGGL(kern, dim3(p->num_tiles), dim3(W * dmas::kWaveSize), 0, nullptr, p->d_mic, p->d_dirs,
                                p->d_tiles, M, p->fs, p->c, p->range, p->mic_block, p->row, p->d_tile_off,
@@ -896,7 +896,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
 
     p->device_bytes = sizeof(double) * 3 * ((size_t)M + (size_t)D) + sizeof(int32_t) * tiles.size() +
                       sizeof(float) * taps.size() + sizeof(float) * (size_t)p->mf_len +
-                      (p->d_tile_off ? sizeof(int32_t) * ((size_t)p->num_tiles * W * M + 2 * dmas::kTableBlockMax +
+                      (p->d_tile_off ? sizeof(int32_t) * ((size_t)p->num_tiles * W * M + dmas::kTableBlockMax +
                                                           (size_t)p->num_tiles * M)
                                      : 0);
 

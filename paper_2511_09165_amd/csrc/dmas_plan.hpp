@@ -55,7 +55,7 @@ struct dmas_plan_s {
     double *d_dirs = nullptr;
     int32_t *d_tiles = nullptr;
     int32_t *d_tile_off = nullptr;    // per-tile delay tables (whole-sample delays), or null
-    int32_t *d_tile_dref = nullptr;
+    int32_t *d_tile_dref = nullptr;   // (in the allocation of d_tile_off)
     float *d_taps = nullptr;
     int env_decim = 1;
     int mf_len = 0;

@@ -57,3 +57,22 @@ def test_plane_free_calls_leave_the_other_launches_as_they_are(M, block, accumul
     for a, b in zip(got["0"], got["1"]):
         np.testing.assert_array_equal(a, b)
     np.testing.assert_array_equal(got["1"][2], got["1"][0])
+
+
+@pytest.mark.parametrize("M", range(4, 20))
+def test_plan_memory_that_a_budget_counts(M):
+    """The device memory a plan reports: geometry, tiles, taps, 36 bytes of tables per tile and
+    microphone and 64 spare; a server whose budget is exactly that and a frame's takes the frame."""
+    from paper_2511_09165_amd import Server, plan_for_frame
+    D, T = 16, 300
+    f = synth.random_frame(np.random.default_rng(M), M, D, T, 3)
+    up = lambda n: (n + 255) & ~255
+    with plan_for_frame(f) as plan:
+        info = plan.info()
+        want = 24 * (M + D) + 32 * info["num_tiles"] + 4 * 64 + 36 * info["num_tiles"] * M + 64
+        assert info["device_bytes"] == want
+        _say(f"budget M={M}: {want} bytes of plan")
+        with Server(up(4 * M * T) + up(4 * D * T) + up(8 * M * T) + up(want), staging=1 << 20) as srv:
+            t = srv.submit(plan, f.x_f32())
+            assert srv.wait(t, 30.0)["t_done"] > 0
+            srv.release(t)
