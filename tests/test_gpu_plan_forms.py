@@ -76,3 +76,31 @@ def test_plan_memory_that_a_budget_counts(M):
             t = srv.submit(plan, f.x_f32())
             assert srv.wait(t, 30.0)["t_done"] > 0
             srv.release(t)
+
+
+def test_rf_frames_are_packed_by_long_walks(monkeypatch, capfd):
+    """A server counts an RF frame's workgroups as long walks, not as the short segments of single
+    calls: two frames whose segments together exceed a launch's cap of two device rounds still
+    share one, with the bits of the calls alone."""
+    from paper_2511_09165_amd import Server, plan_for_frame
+    monkeypatch.setenv("DMAS_SMALL_LAUNCH_WGS", "0")          # frames behind the first wait and are packed
+    first = synth.random_frame(np.random.default_rng(1), 32, 4096, 16384, 5)
+    f = synth.random_frame(np.random.default_rng(2), 16, 600, 4096, 3)
+    plan, log = _logged(capfd, monkeypatch, f)
+    tiles, walks = int(log["tiles"]), int(log["nseg"].split("/")[0])
+    calls = -(-4096 // int(log["call"]))
+    cap = 2 * 3 * torch.cuda.get_device_properties(0).multi_processor_count
+    _say(f"packing: {tiles} tiles, {walks} walks, {calls} segments, cap {cap}")
+    assert 2 * tiles * walks <= cap < 2 * tiles * calls
+    with plan, plan_for_frame(first) as plan1, Server(4 << 30, staging=64 << 20) as srv:
+        ref = plan.beamform(torch.from_numpy(f.x_f32()).cuda()).cpu().numpy()
+        x1, x = first.x_f32(), f.x_f32()
+        heads = [srv.submit(plan1, x1) for _ in range(2)]
+        tickets = [srv.submit(plan, x, envelope=False) for _ in range(8)]
+        infos = [srv.wait(t, 30.0) for t in tickets]
+        assert max(i["batch_frames"] for i in infos) >= 2
+        for t in tickets:
+            np.testing.assert_array_equal(srv.fetch(t), ref)
+        for t in tickets + heads:
+            srv.wait(t, 30.0)
+            srv.release(t)
