@@ -104,15 +104,16 @@ constexpr int kChunk = kWaveSize * kSamplesPerLane;
 
 // A launch has fewer than 2^32 threads in each grid dimension: the most
 // workgroups of the beamformer, and the root pass's grid for M rows of stride
-// pairs, where a workgroup of kRootThreads takes kRootBlock pairs of one row
-// (rows past grid_y go round again).
+// pairs, where a workgroup of kRootThreads takes `block` pairs of one row (rows
+// past grid_y go round again).
 constexpr int64_t kMaxWorkgroups = UINT32_MAX / (kDirsPerTile * kWaveSize);
 constexpr int kRootThreads = 256;
 constexpr int kRootBlock = 4 * kRootThreads;
 constexpr int kRootMaxRows = 65535;
-inline void root_grid(int M, int stride, unsigned *grid_x, unsigned *grid_y)
+constexpr int64_t kRootWide = 1 << 18;   // elements of a plane up to which a thread takes one
+inline void root_grid(int M, int stride, unsigned *grid_x, unsigned *grid_y, int block = kRootBlock)
 {
-    *grid_x = (unsigned)(stride / kRootBlock) + (stride % kRootBlock != 0);
+    *grid_x = (unsigned)(stride / block) + (stride % block != 0);
     *grid_y = (unsigned)(M < kRootMaxRows ? M : kRootMaxRows);
 }
 

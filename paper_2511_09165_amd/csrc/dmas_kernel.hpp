@@ -248,23 +248,27 @@ constexpr bool kStagesRoots = N >= 2 && !LINEAR;
 
 // Root plane: row i holds (signed_root(x), x) of channel i's samples at
 // [pad0, pad0 + T) and zero pairs elsewhere in its `stride` elements. A
-// workgroup takes kRootBlock elements of row blockIdx.y and of every
-// gridDim.y-th after it.
-template <int N, int DT>
+// workgroup takes J elements a thread of row blockIdx.y and of every
+// gridDim.y-th after it: one on planes up to kRootWide elements, which with
+// four would not give every compute unit a workgroup (16 x 2048: 2.4 us, with
+// four 2.9; 32 x 4096 2.4 and 2.9; of 30 such frames served behind a long one the
+// last was done at 890 us instead of 930), four on larger ones (1024 x 4096: 11.5
+// us, with one 12.3; calls on 64 x 8192 FP16 samples 0.5 us faster).
+template <int N, int DT, int J>
 __global__ void __launch_bounds__(kRootThreads)
 root_plane_kernel(const void *__restrict__ x, float2 *__restrict__ plane, int M, int T, int pad0, int stride)
 {
-    const int e0 = blockIdx.x * kRootBlock + threadIdx.x;
+    const int e0 = blockIdx.x * (J * kRootThreads) + threadIdx.x;
     for (int mic = blockIdx.y; mic < M; mic += gridDim.y) {
         const size_t chan = (size_t)mic * (size_t)T, row = (size_t)mic * (size_t)stride;
-        float v[4];
+        float v[J];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < J; ++j) {
             const int t = e0 + j * kRootThreads - pad0;
             v[j] = t >= 0 && t < T ? load_sample<DT>(x, chan + (size_t)t) : 0.0f;
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < J; ++j) {
             const int e = e0 + j * kRootThreads;
             if (e < stride) plane[row + (size_t)e] = make_float2(signed_root<N, true>(v[j]), v[j]);
         }

@@ -226,3 +226,17 @@ def test_root_plane_of_more_rows_than_a_grid_dimension(monkeypatch):
     np.testing.assert_array_equal(got["0"], got["1"])
     taps = oracle.lowpass_taps(63, 5000.0, f.fs).astype(np.float32).astype(np.float64)
     check_t1(got["0"], oracle.envelope(oracle.frame_rows(f, x=f.x_f32().astype(np.float64)), taps))
+
+
+@pytest.mark.parametrize("M,T", [(8, 255), (8, 257), (64, 3680), (64, 3681), (130, 40001)])
+def test_root_plane_with_one_and_four_elements_a_thread(M, T, monkeypatch):
+    """Planes below and above 2^18 elements, rows on and off the workgroups' blocks: the bits of
+    roots taken while staging."""
+    f = synth.random_frame(np.random.default_rng(M + T), M, 9, T, 3)
+    f.x[0, 0], f.x[M - 1, T - 1] = np.inf, np.nan                    # the plane's first and last samples
+    _say(f"root plane {M} x {T}")
+    got = {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        got[direct] = _image(f, f.x_f32())
+    np.testing.assert_array_equal(got["0"], got["1"])
