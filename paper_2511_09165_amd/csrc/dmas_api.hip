@@ -304,7 +304,7 @@ bool two_pass_pays(const dmas_plan_s *p)
     const double slots = p->order + 2 + (p->linear ? 6 : 0);           // VALU slots per microphone and pixel
     const double rf = pixels * p->M * slots / 33e12 * (p->compensated ? 2 : 1);   // seconds
     const double loss = (p->order > 5 ? 0.3 : 0.2) * (p->linear ? 0.5 : 1.0);
-    return (int64_t)p->num_tiles * p->nseg_call >= 2 * (int64_t)p->cus && 4 * pixels <= kImageInCache &&
+    return (int64_t)p->num_tiles * p->nseg_rf >= 2 * (int64_t)p->cus && 4 * pixels <= kImageInCache &&
            loss * rf > 0.3e-12 * pixels + 4e-6;
 }
 
@@ -914,13 +914,13 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         if (env)
             choose_segments(T, p->num_tiles, H, slots, seg_override, &p->seg_env, &p->nseg_env);
         else
-            choose_segments(T, p->num_tiles, 0, slots, seg_override, &p->seg_rf, &p->nseg_rf);
-        if (!env) dmas::choose_rf_segments(T, p->num_tiles, slots, seg_override, &p->seg_call, &p->nseg_call);
+            choose_segments(T, p->num_tiles, 0, slots, seg_override, &p->seg_walk, &p->nseg_walk);
+        if (!env) dmas::choose_rf_segments(T, p->num_tiles, slots, seg_override, &p->seg_rf, &p->nseg_rf);
         if (env) p->occ_env = blocks; else p->occ_rf = blocks;
     }
     p->two_pass = decim == 1 && two_pass_pays(p);
     if (const char *ep = std::getenv("DMAS_ENVELOPE_PASSES")) p->two_pass = decim == 1 && std::atoi(ep) == 2;
-    if ((int64_t)p->num_tiles * std::max({p->nseg_rf, p->nseg_env, p->nseg_call}) > INT32_MAX) {
+    if ((int64_t)p->num_tiles * std::max({p->nseg_rf, p->nseg_env, p->nseg_walk}) > INT32_MAX) {
         plan_free(p);
         return fail(DMAS_ERR_UNSUPPORTED, "grid too large");
     }
@@ -928,8 +928,8 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
         fprintf(stderr,
                 "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d range=%d row=%d mb=%d seg=%d/%d nseg=%d/%d call=%d lds=%zu/%zu "
                 "occupancy=%d/%d tables=%s direct=%d pads=%d/%d\n",
-                M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_rf, p->seg_env, p->nseg_rf,
-                p->nseg_env, p->seg_call, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env,
+                M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_walk, p->seg_env, p->nseg_walk,
+                p->nseg_env, p->seg_rf, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env,
                 !p->tables ? "none" : !p->block_tables ? "mics" : p->share_rings ? "blocks,shared" : "blocks",
                 p->direct ? p->direct_block : 0, p->pad0, p->pad1);
     *out = p;

@@ -47,9 +47,9 @@ struct dmas_plan_s {
     int direct_block = 0;  // microphones per LDS block of the launches without a root plane
     int row = 0;
     bool two_pass = false; // envelope calls: RF image into the output, then the filter over it in place
-    int seg_rf = 0, seg_env = 0;   // samples per workgroup (a server's RF launches and all envelopes)
+    int seg_rf = 0, seg_env = 0;   // samples per workgroup of a launch
     int nseg_rf = 0, nseg_env = 0;
-    int seg_call = 0, nseg_call = 0;   // the same of single RF launches
+    int seg_walk = 0, nseg_walk = 0;   // RF frames: those of a resident worker, and what a server counts
     size_t lds_rf = 0, lds_env = 0;
     int occ_rf = 0, occ_env = 0;
     double *d_mic = nullptr;
@@ -121,11 +121,12 @@ inline hipError_t allocate_plane(const dmas_plan_s *plan, Alloc &&alloc, float2 
     return e;
 }
 
-// Output samples per workgroup of a single RF launch: segments share nothing, so
-// a cut costs only the workgroup's setup. (A server's launches keep the long
-// walks: its grouping counts workgroups as those, and a resident worker claims
-// them one at a time. Segments like these there: 48 mixed RF frames of 16-64
-// microphones 2.79 -> 2.95 ms batched, 7.9 -> 10.3 ms resident.) One to three chunks, so that each of
+// Output samples per workgroup of an RF launch: segments share nothing, so a cut
+// costs only the workgroup's setup. (A server's grouping counts such frames as
+// the long walks of plan_walks, which its caps are set for, and resident workers,
+// which claim them one at a time, take those. 48 mixed RF frames of 16-64
+// microphones 2.66 ms batched, counted as segments 2.93, both in walks 2.82; 7.9
+// ms resident, in segments 10.3.) One to three chunks, so that each of
 // `slots` places gets four workgroups where the record allows; more where the
 // launch would not hold the workgroups (kMaxWorkgroups: with three chunks,
 // images of 5e10 pixels and up). fixed > 0: that many, rounded up to 32.
@@ -151,8 +152,7 @@ inline hipError_t stage_roots(const dmas_plan_s *plan, const void *d_x, float2 *
                         padded ? plan->pad1 : 0, stream);
 }
 
-// Kernel arguments for a server's launch of `plan` (single calls:
-// launch_image) on input d_x (and its root plane
+// Kernel arguments for one launch of `plan` on input d_x (and its root plane
 // d_plane when the plan uses one) / output d_out.
 inline KernelParams make_params(const dmas_plan_s *plan, const void *d_x, const float2 *d_plane, float *d_out,
                                 float in_scale, bool env, bool padded = false)
@@ -231,10 +231,17 @@ inline int direct_block_of(int mic_block, int M, int cap)
     return b;
 }
 
-// Workgroups of a server's launch of the plan.
+// Workgroups of one launch of the plan.
 inline int64_t plan_workgroups(const dmas_plan_s *p, bool env)
 {
     return (int64_t)p->num_tiles * (env ? p->nseg_env : p->nseg_rf);
+}
+
+// The same with segments as long as the makespan allows: what a server counts a
+// frame as, in device rounds, and the items of a resident worker.
+inline int64_t plan_walks(const dmas_plan_s *p, bool env)
+{
+    return (int64_t)p->num_tiles * (env ? p->nseg_env : p->nseg_walk);
 }
 
 // Record the calling thread's last error message (returned by dmas_last_error).
@@ -251,12 +258,8 @@ inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const f
 {
     const bool fused = env && !plan->two_pass;
     KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused, padded);
-    LaunchShape ls = plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused);
+    const LaunchShape ls = plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused);
     if (plan->direct) kp.mic_block = plan->direct_block;
-    if (!fused) {
-        kp.seg_len = plan->seg_call;
-        ls.grid = (unsigned)((int64_t)plan->num_tiles * plan->nseg_call);
-    }
     hipError_t e = launch_plan(plan->order, &kp, ls, stream);
     if (e == hipSuccess && env && !fused)
         e = launch_envelope_rows(d_out, plan->d_taps, plan->D, plan->T, plan->fir_len, plan->seg_env, plan->cus,

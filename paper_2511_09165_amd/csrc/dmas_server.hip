@@ -422,7 +422,7 @@ struct dmas_server_s {
             std::vector<dmas::sched::Candidate> cand;
             cand.reserve(admitted.size());
             for (Frame *f : admitted)
-                cand.push_back({kernel_class(f), batchable(f->plan), dmas::plan_workgroups(f->plan, f->env)});
+                cand.push_back({kernel_class(f), batchable(f->plan), dmas::plan_walks(f->plan, f->env)});
             const dmas::sched::LaunchPick lp =
                 dmas::sched::pick_launch(ss, now_s(), cand, max_batch, batch_wg_cap, small_wg_cap);
             if (lp.stream < 0) break;
@@ -485,7 +485,7 @@ struct dmas_server_s {
                 int64_t wgs = 0;
                 for (Frame *f : group) {
                     work += frame_work(f->plan, f->env);
-                    wgs += dmas::plan_workgroups(f->plan, f->env);
+                    wgs += dmas::plan_walks(f->plan, f->env);
                 }
                 bool alone = true;
                 for (auto &other : launches)
@@ -531,7 +531,7 @@ struct dmas_server_s {
     // A frame whose pixels job is done.
     void res_finish(Frame *f)
     {
-        res_queued_items -= dmas::plan_workgroups(f->plan, f->env);
+        res_queued_items -= dmas::plan_walks(f->plan, f->env);
         const bool ok = __atomic_load_n(&res_h->error, __ATOMIC_ACQUIRE) == 0;
         f->t_done = now_s();
         f->state = ok ? kDone : kFailed;
@@ -637,7 +637,7 @@ struct dmas_server_s {
         j.kp = res_params(f);
         j.kind = dmas::kJobPixels;
         j.count = 0;
-        j.items = (int32_t)dmas::plan_workgroups(f->plan, f->env);
+        j.items = (int32_t)dmas::plan_walks(f->plan, f->env);
         j.dep = f->res_roots_job;
         j.dep_items = f->res_roots_items;
         j.epoch = res_epoch;
@@ -650,8 +650,10 @@ struct dmas_server_s {
 
     dmas::KernelParams res_params(const Frame *f) const
     {
-        return dmas::make_params(f->plan, d_staging + f->stage_off, plane_of(f),
-                                 reinterpret_cast<float *>(d_arena + f->out_off), f->in_scale, f->env);
+        dmas::KernelParams kp = dmas::make_params(f->plan, d_staging + f->stage_off, plane_of(f),
+                                                  reinterpret_cast<float *>(d_arena + f->out_off), f->in_scale, f->env);
+        if (!f->env) kp.seg_len = f->plan->seg_walk;
+        return kp;
     }
 
     bool res_same_class(const Frame *f) const
