@@ -126,6 +126,13 @@ dmas_status_t srv_fail(dmas_status_t st, const char *msg)
 constexpr int32_t kResidentIdlePolls = 2000;
 constexpr int32_t kResidentDepPolls = 1 << 22;
 constexpr double kResidentLife = 0.100;
+// Worker workgroups per compute unit: each reads every job's descriptor from
+// host memory and writes the L2 back once per job, so more of them than the
+// sums need cost more than they give. Three or four, which registers and LDS
+// allow, against two: 30 envelopes of 32 microphones, 600 x 4096 at order 5 4.7
+// and 3.65 ms, 48 mixed envelopes of 16-64 microphones 8.2 and 6.9, RF images 8.2
+// and 6.5, four of 4186 x 16384 3.0 and 2.95.
+constexpr int kResidentBlocksPerCu = 2;
 constexpr double kResidentSwitchWait = 0.001;   // DMAS_RESIDENT_SWITCH_US overrides
 constexpr double kEpochMin = 0.002;             // shortest memory epoch
 
@@ -585,6 +592,9 @@ struct dmas_server_s {
         if (e == hipSuccess)
             e = dmas::launch_resident(res_order, res_cf, res_env, res_near, res_delay, a, 0, res_lds, res_stream, &blocks);
         if (e == hipSuccess && blocks < 1) e = hipErrorInvalidConfiguration;
+        blocks = std::min(blocks, kResidentBlocksPerCu);
+        if (std::getenv("DMAS_LOG"))
+            fprintf(stderr, "[dmas] resident worker n=%d env=%d workgroups=%d\n", res_order, (int)res_env, blocks * res_cus);
         res_items_cap = (int64_t)16 * blocks * res_cus;
         if (e == hipSuccess)
             e = dmas::launch_resident(res_order, res_cf, res_env, res_near, res_delay, a, (unsigned)(blocks * res_cus),

@@ -104,3 +104,27 @@ def test_rf_frames_are_packed_by_long_walks(monkeypatch, capfd):
         for t in tickets + heads:
             srv.wait(t, 30.0)
             srv.release(t)
+
+
+@pytest.mark.parametrize("n", [3, 5])
+@pytest.mark.parametrize("envelope", [False, True])
+def test_resident_workers_take_two_workgroups_a_unit(n, envelope, monkeypatch, capfd):
+    """Small windows would let three or four worker workgroups share a compute unit; each costs a
+    descriptor read and a write-back per job, and two serve frames faster."""
+    from paper_2511_09165_amd import Server, plan_for_frame
+    monkeypatch.setenv("DMAS_LOG", "1")
+    f = synth.random_frame(np.random.default_rng(n), 16, 200, 900, n)
+    f.mic_pos = f.mic_pos * 0.1
+    x = f.x_f32()
+    _say(f"resident workgroups n={n} envelope={envelope}")
+    with plan_for_frame(f) as plan, Server(64 << 20, staging=4 << 20, resident=True) as srv:
+        xt = torch.from_numpy(x).cuda()
+        ref = (plan.envelope(xt) if envelope else plan.beamform(xt)).cpu().numpy()
+        capfd.readouterr()
+        t = srv.submit(plan, x, envelope=envelope)
+        srv.wait(t, 30.0)
+        np.testing.assert_array_equal(srv.fetch(t), ref)
+        srv.release(t)
+    logged = re.findall(r"resident worker n=(\d) env=(\d) workgroups=(\d+)", capfd.readouterr().err)
+    assert logged and logged[0][:2] == (str(n), str(int(envelope)))
+    assert int(logged[0][2]) == 2 * torch.cuda.get_device_properties(0).multi_processor_count
