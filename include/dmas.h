@@ -123,7 +123,11 @@ typedef struct {
     int32_t mf_len;        /* 0..DMAS_MAX_MF_LEN */
 } dmas_plan_desc_t;
 
-/* Read-only facts about a created plan (tiling chosen for the device). */
+/* Read-only facts about a created plan (tiling chosen for the device). The
+ * segments, LDS and workgroups are those of the beamforming kernel that filters
+ * the envelope itself and reads a root plane, the one a server launches: a single
+ * dmas_envelope may filter in a second kernel or use no root plane (DMAS_LOG
+ * prints which, dmas_plan_create). */
 typedef struct {
     int32_t num_mics, num_samples, num_dirs, order;
     int32_t dirs_per_tile;     /* directions sharing one staged channel window */
@@ -167,7 +171,9 @@ dmas_status_t dmas_plan_desc_init(dmas_plan_desc_t *desc);
  * the RF image in d_env, DMAS_DIRECT_ROOTS=0/1 whether calls on a plan with
  * tables take the signed roots while staging the channel windows instead of
  * from a root plane (a choice made only where DMAS_RING_SHARING is not set),
- * DMAS_LOG prints the plan's choices and errors to stderr. */
+ * DMAS_LOG prints the plan's choices (direct: microphones per block of calls
+ * without a root plane, 0 where they use one; passes: 1 or 2 kernels of an
+ * envelope) and errors to stderr. */
 dmas_status_t dmas_plan_create(const dmas_plan_desc_t *desc, dmas_plan_t *out);
 
 /* Release a plan and its device memory. NULL is a no-op. Work queued with

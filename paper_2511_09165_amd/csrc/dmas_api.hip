@@ -927,11 +927,11 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     if (std::getenv("DMAS_LOG"))
         fprintf(stderr,
                 "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d range=%d row=%d mb=%d seg=%d/%d nseg=%d/%d call=%d lds=%zu/%zu "
-                "occupancy=%d/%d tables=%s direct=%d pads=%d/%d\n",
+                "occupancy=%d/%d tables=%s direct=%d passes=%d pads=%d/%d\n",
                 M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_walk, p->seg_env, p->nseg_walk,
                 p->nseg_env, p->seg_rf, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env,
                 !p->tables ? "none" : !p->block_tables ? "mics" : p->share_rings ? "blocks,shared" : "blocks",
-                p->direct ? p->direct_block : 0, p->pad0, p->pad1);
+                p->direct ? p->direct_block : 0, p->two_pass ? 2 : 1, p->pad0, p->pad1);
     *out = p;
     return DMAS_OK;
 }

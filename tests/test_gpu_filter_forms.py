@@ -60,3 +60,24 @@ def test_both_forms_agree_where_pixels_are_not_finite(L, segment, monkeypatch):
             away[max(0, p - H - 17):p + H + 16] = False
         np.testing.assert_array_equal(b[:, away], two[0][:, away])
         assert all(np.isnan(b[:, max(0, p - H):p + H + 1]).all() for p in t[1::2])   # the NaN ones
+
+
+# more rows than the pass has workgroups (eight a compute unit), of two steps and a little more: a
+# workgroup goes from the end of one row to the start of another; rows on and off the 16-byte grid
+@pytest.mark.parametrize("L", [1, 63, 255])
+@pytest.mark.parametrize("D,T", [(2100, 2049), (4300, 2113), (2500, 4100), (4200, 2048)])
+def test_workgroups_that_walk_several_long_rows(L, D, T, monkeypatch):
+    """Rows of several steps, two or three a workgroup: the fused filter's bits in every row."""
+    assert D > 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    f = synth.random_frame(np.random.default_rng(D + T + L), 2, D, T, 2)
+    taps = np.random.default_rng(L).normal(size=L).astype(np.float32)
+    x = f.x_f32()
+    _say(f"rows of several steps D={D} T={T} L={L}")
+    one, two = _both(f, [x, np.ascontiguousarray(x[:, ::-1])], monkeypatch, fir_taps=taps)
+    for a, b in zip(one, two):
+        np.testing.assert_array_equal(b, a)
+    rows = [0, 1, D // 2, D - 1]
+    g = synth.random_frame(np.random.default_rng(D + T + L), 2, D, T, 2)
+    g.dirs = g.dirs[rows]
+    y_ref = oracle.frame_rows(g, x=x.astype(np.float64))
+    check_t1(two[0][rows], oracle.envelope(y_ref, taps.astype(np.float64)))

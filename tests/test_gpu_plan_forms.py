@@ -128,3 +128,64 @@ def test_resident_workers_take_two_workgroups_a_unit(n, envelope, monkeypatch, c
     logged = re.findall(r"resident worker n=(\d) env=(\d) workgroups=(\d+)", capfd.readouterr().err)
     assert logged and logged[0][:2] == (str(n), str(int(envelope)))
     assert int(logged[0][2]) == 2 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def test_overrides_choose_the_forms(monkeypatch, capfd):
+    """The overrides that the tests of equal forms rely on do choose the form, on either side of the
+    plan's own choice; a form that cannot run is not chosen."""
+    small = synth.random_frame(np.random.default_rng(3), 8, 20, 500, 3)
+    large = synth.random_frame(np.random.default_rng(4), 64, 1200, 8192, 3)
+
+    def forms(f, env, **kw):
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        plan, log = _logged(capfd, monkeypatch, f, **kw)
+        plan.close()
+        for k in env:
+            monkeypatch.delenv(k)
+        return log["direct"] != "0", int(log["passes"])
+
+    _say("plan forms")
+    assert forms(small, {}) == (True, 1)
+    assert forms(large, {}) == (False, 2)
+    for f in (small, large):
+        for direct in (False, True):
+            for passes in (1, 2):
+                env = {"DMAS_DIRECT_ROOTS": str(int(direct)), "DMAS_ENVELOPE_PASSES": str(passes)}
+                assert forms(f, env) == (direct, passes)
+    force = {"DMAS_DIRECT_ROOTS": "1", "DMAS_ENVELOPE_PASSES": "2"}
+    assert forms(small, force, env_decimation=2) == (True, 1)              # decimated: the fused filter
+    assert forms(small, force, linear=True) == (False, 2)          # no roots
+    assert forms(small, dict(force, DMAS_NO_DELAY_TABLE="1")) == (False, 2)
+    assert forms(small, dict(force, DMAS_RING_SHARING="1")) == (False, 2)
+    assert forms(small, dict(force, DMAS_BLOCK_TABLES="0")) == (False, 2)
+
+
+def test_plane_free_plan_in_a_graph(monkeypatch, capfd):
+    """A plan whose calls use no root plane, and one in two passes, replay from a graph with eager
+    calls between the replays."""
+    monkeypatch.setenv("DMAS_DIRECT_ROOTS", "1")
+    monkeypatch.setenv("DMAS_ENVELOPE_PASSES", "2")
+    f = synth.random_frame(np.random.default_rng(6), 12, 40, 2500, 3)
+    plan, log = _logged(capfd, monkeypatch, f)
+    assert log["direct"] != "0" and log["passes"] == "2"
+    _say("plane-free two-pass plan in a graph")
+    with plan:
+        x = torch.from_numpy(f.x_f32()).cuda()
+        ref = plan.envelope(x)
+        out = torch.empty_like(ref)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            plan.envelope(x, out=out)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            plan.envelope(x, out=out)
+        for _ in range(3):
+            out.fill_(float("nan"))
+            g.replay()
+            with torch.cuda.stream(side):
+                other = plan.envelope(x)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref) and torch.equal(other, ref)
