@@ -19,6 +19,7 @@
 // step ahead and barriers that wait for LDS only brought it there from 190 us;
 // a block's operand reads ahead of its products took another 2 us off small
 // images (361 x 4096: 10.8 -> 8.9 us).
+#include "dmas_barrier.hpp"
 #include "dmas_internal.hpp"
 
 namespace dmas {
@@ -43,15 +44,6 @@ __host__ __device__ constexpr int row_plane(int H) { return ((row_logical(H) / 4
 __host__ __device__ constexpr int row_floats(int H) { return 4 * row_plane(H); }
 // Output staging of a wave whose rows are not 16-byte aligned.
 constexpr int kRowStage = kChunk;
-
-// Barrier for LDS traffic alone: the workgroup's global loads and stores in
-// flight (the next step's samples, this step's outputs) are not waited for.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // A workgroup walks whole rows, blockIdx.x and every gridDim.x-th after it, in
 // steps of kRowBlock outputs, and loads the next step's samples while it works

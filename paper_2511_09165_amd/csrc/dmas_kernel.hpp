@@ -50,6 +50,7 @@
 #include <type_traits>
 
 #include "dmas.h"
+#include "dmas_barrier.hpp"
 #include "dmas_internal.hpp"
 
 namespace dmas {
@@ -599,15 +600,6 @@ __device__ __forceinline__ float2 lds_pair(const float2 *p)
     typedef float v2f __attribute__((ext_vector_type(2)));
     const v2f v = *(const volatile __attribute__((address_space(3))) v2f *)p;
     return make_float2(v.x, v.y);
-}
-
-// Barrier for LDS traffic alone: global stores in flight (the previous chunk's
-// outputs) are not waited for.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // ---------------------------------------------------------------------------
