@@ -195,7 +195,9 @@ dmas_status_t dmas_plan_query(dmas_plan_t plan, dmas_plan_info_t *info);
  * in flight, and where the device has room zeros around each row for the
  * largest delay and a chunk, at most 256 MiB), so one plan may be used on
  * several streams at once. Small frames take the same roots inside the
- * beamformer and use no plane. Errors:
+ * beamformer and use no plane, unless d_y lies over d_x (which a plane allows,
+ * the channels being read before anything is written; with n = 1 or LINEAR
+ * delays they must not overlap). Errors:
  * DMAS_ERR_INVALID_ARG (NULL pointers, in_scale, plan of another device),
  * DMAS_ERR_OUT_OF_MEMORY (plane allocation), DMAS_ERR_DEVICE (launch). */
 dmas_status_t dmas_beamform(dmas_plan_t plan, const void *d_x, float *d_y,

@@ -514,6 +514,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
     hipStream_t st = static_cast<hipStream_t>(stream);
     float2 *plane = nullptr;
     bool padded = false;
+    const bool direct = dmas::call_direct(plan, d_x, d_out, env);
     hipError_t e = hipSuccess;
     if (plan->roots && noalloc) {
         const size_t need = dmas::plane_bytes(plan);
@@ -524,21 +525,21 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
                         need, plan->M, plan->T, (size_t)DMAS_NOALLOC_SCRATCH_BYTES);
         float2 *fixed = nullptr;
         padded = dmas::padded_plane_bytes(plan) <= DMAS_NOALLOC_SCRATCH_BYTES;
-        if (!plan->direct) {
+        if (!direct) {
             e = scratch_address(plan->device, &fixed);
             if (e != hipSuccess) return hip_fail(e, "address of the fixed root-plane scratch");
             // every element the kernel reads is written here first: nothing needs clearing
             e = dmas::stage_roots(plan, d_x, fixed, padded, st);
             if (e != hipSuccess) return hip_fail(e, "root-plane launch");
         }
-        e = dmas::launch_image(plan, d_x, fixed, padded, d_out, in_scale, env, st);
+        e = dmas::launch_image(plan, d_x, fixed, padded, direct, d_out, in_scale, env, st);
         if (e == hipErrorNotSupported)
             return fail(DMAS_ERR_UNSUPPORTED, "no kernel for order %d cf=%d env=%d near=%d accumulate=%d",
                         plan->order, (int)plan->cf, (int)env, (int)plan->nearfield, (int)plan->compensated);
         if (e != hipSuccess) return hip_fail(e, "kernel launch");
         return DMAS_OK;
     }
-    if (plan->roots && !plan->direct) {
+    if (plan->roots && !direct) {
         hipMemPool_t pool = nullptr;
         e = device_pool(plan->device, &pool);
         if (e != hipSuccess) return hip_fail(e, "root-plane memory pool");
@@ -551,7 +552,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
             return hip_fail(e, "root-plane launch");
         }
     }
-    e = dmas::launch_image(plan, d_x, plane, padded, d_out, in_scale, env, st);
+    e = dmas::launch_image(plan, d_x, plane, padded, direct, d_out, in_scale, env, st);
     if (plane) {
         const hipError_t ef = hipFreeAsync(plane, st);
         if (e == hipSuccess) e = ef;

@@ -251,15 +251,27 @@ void set_last_error(const char *msg);
 hipError_t launch_plan(int order, const KernelParams *kp, const LaunchShape &ls, hipStream_t st,
                        int *blocks = nullptr);
 
+// Whether a call takes the roots while staging: the plan's choice, but not where
+// the output shares memory with the channels, which a root plane copies first.
+inline bool call_direct(const dmas_plan_s *p, const void *d_x, const float *d_out, bool env)
+{
+    const size_t in = (size_t)p->M * (size_t)p->T * (p->dtype == DMAS_F32 ? 4 : 2);
+    const size_t T = env ? ((size_t)p->T + p->env_decim - 1) / p->env_decim : (size_t)p->T;
+    const uintptr_t x = reinterpret_cast<uintptr_t>(d_x), y = reinterpret_cast<uintptr_t>(d_out);
+    const bool apart = x + in <= y || y + (size_t)p->D * T * sizeof(float) <= x;
+    return p->direct && apart;
+}
+
 // Launch the beamformer of one call and, for an envelope in two passes, the
 // filter over its image (d_plane filled before, in stream order).
+// direct: without a root plane.
 inline hipError_t launch_image(const dmas_plan_s *plan, const void *d_x, const float2 *d_plane, bool padded,
-                               float *d_out, float in_scale, bool env, hipStream_t stream)
+                               bool direct, float *d_out, float in_scale, bool env, hipStream_t stream)
 {
     const bool fused = env && !plan->two_pass;
     KernelParams kp = make_params(plan, d_x, d_plane, d_out, in_scale, fused, padded);
-    const LaunchShape ls = plan->direct ? direct_shape_of(plan, fused) : shape_of(plan, fused);
-    if (plan->direct) kp.mic_block = plan->direct_block;
+    const LaunchShape ls = direct ? direct_shape_of(plan, fused) : shape_of(plan, fused);
+    if (direct) kp.mic_block = plan->direct_block;
     hipError_t e = launch_plan(plan->order, &kp, ls, stream);
     if (e == hipSuccess && env && !fused)
         e = launch_envelope_rows(d_out, plan->d_taps, plan->D, plan->T, plan->fir_len, plan->seg_env, plan->cus,

@@ -189,3 +189,29 @@ def test_plane_free_plan_in_a_graph(monkeypatch, capfd):
                 other = plan.envelope(x)
             torch.cuda.synchronize()
             assert torch.equal(out, ref) and torch.equal(other, ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("place", ["start", "end", "before", "behind"])
+def test_output_over_the_channels(place, dtype, monkeypatch, capfd):
+    """A plan with roots reads its channels into a root plane before it writes, so an output may lie
+    over them; a plan whose calls use no plane does so too, and where the two only touch it does
+    not need to."""
+    monkeypatch.setenv("DMAS_DIRECT_ROOTS", "1")
+    f = synth.random_frame(np.random.default_rng(8), 48, 400, 4000, 3)
+    plan, log = _logged(capfd, monkeypatch, f, in_dtype=dtype)
+    assert log["direct"] != "0"
+    _say(f"output over the channels: {place} {dtype}")
+    xt = torch.from_numpy(f.x_f32()).cuda().to({"f32": torch.float32, "bf16": torch.bfloat16}[dtype])
+    xb, yb = xt.numel() * xt.element_size(), 4 * f.num_dirs * f.num_samples
+    x_at, y_at = {"start": (0, 0), "end": (yb - xb, 0), "before": (yb, 0), "behind": (0, xb)}[place]
+    with plan:
+        ref = [plan.beamform(xt), plan.envelope(xt)]
+        for _ in range(5):
+            for call, want in zip((plan.beamform, plan.envelope, plan.envelope_noalloc), ref + ref[1:]):
+                buf = torch.zeros(xb + yb, dtype=torch.uint8, device="cuda")
+                x = buf[x_at:x_at + xb].view(xt.dtype).view(xt.shape)
+                y = buf[y_at:y_at + yb].view(torch.float32).view(want.shape)
+                x.copy_(xt)
+                call(x, y) if call == plan.envelope_noalloc else call(x, out=y)
+                assert torch.equal(y, want)
