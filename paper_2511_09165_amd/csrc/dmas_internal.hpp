@@ -42,9 +42,6 @@ struct KernelParams {
                               // |delay - reference delay| within a tile; 0 with tables
     int32_t row;              // LDS row length per microphone (floats)
     int32_t mic_block;        // microphones per LDS block, <= kMaxMicBlock
-    int32_t table_block;      // the block that tile_off was built for: mic_block, but with
-                              // kDelayTableDirect and Kahan or FP64 sums also a multiple of
-                              // it or at least M
     int32_t dtype;            // dmas_dtype_t
     int32_t ng_fp64;          // evaluate Newton-Girard in FP64
     double fs, c;
@@ -53,6 +50,9 @@ struct KernelParams {
     int32_t env_decim;        // envelope keeps every env_decim-th sample
     int32_t plane_stride, plane_lo, plane_hi;   // layout of roots
     int32_t out_T;            // output row length: T, or ceil(T / env_decim) for the envelope
+    int32_t table_block;      // the block that tile_off was built for: mic_block, but with
+                              // kDelayTableDirect and Kahan or FP64 sums also a multiple of
+                              // it or at least M
 };
 
 // A batch of frames for the multi-frame kernel (device pointers).
