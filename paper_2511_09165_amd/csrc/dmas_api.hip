@@ -264,7 +264,7 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
 // Whether a single call takes the roots while staging instead of reading them
 // from a root plane (the same bits). The plane costs a launch (2-3 us) and a pool
 // allocation and free around the call (about 15 us of host time, which bounds
-// calls whose kernels are shorter than 30 us); without it a sample's root is
+// calls whose kernels are shorter than 23-33 us, depending on the box); without it a sample's root is
 // taken again in every window that holds it, work that grows with the windows'
 // elements, and every block of 16 microphones waits for its loads in turn.
 // Measured over 45 frames (back to back, plane against direct): 8 microphones, 64
