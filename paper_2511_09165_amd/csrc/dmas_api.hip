@@ -264,9 +264,10 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
 // Whether a single call takes the roots while staging instead of reading them
 // from a root plane (the same bits). The plane costs a launch (2-3 us) and a pool
 // allocation and free around the call (about 15 us of host time, which bounds
-// calls whose kernels are shorter than 23-33 us, depending on the box); without it a sample's root is
-// taken again in every window that holds it, work that grows with the windows'
-// elements, and every block of 16 microphones waits for its loads in turn.
+// calls whose kernels are shorter than 23-33 us, depending on the box); without
+// it a sample's root is taken again in every window that holds it, work that
+// grows with the windows' elements, and every block of 16 microphones waits for
+// its loads in turn.
 // Measured over 45 frames (back to back, plane against direct): 8 microphones, 64
 // x 1024 at order 2 33.0 and 9.9 us, 19, 181 x 3001 at order 3 25.1 and 11.6, 57,
 // 78 x 4725 at order 6 29.9 and 16.9, 30, 145 x 14067 at order 3 (6.5e7 elements)
@@ -787,11 +788,12 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     // fits) and the workgroups per CU at that block.
     // (and no more than the chunks of the record give every compute unit: with
     // fewer workgroups than that larger blocks are faster, 241 microphones,
-    // 64 x 2480 at order 2 46.8 -> 41.4 us)
+    // 64 x 2480 at order 2 46.8 -> 41.4 us; not without tables, whose blocks can
+    // grow to 64: 512 microphones, 240 x 2048 at order 4 171 -> 204 us)
     const int64_t chunk_wgs = (int64_t)p->num_tiles * ((T + C - 1) / C);
-    const int occ_target = M <= dmas::kWaveSize
-                               ? 3
-                               : (int)std::min<int64_t>(1 << 30, (chunk_wgs + p->cus - 1) / p->cus);
+    const int occ_target = M <= dmas::kWaveSize ? 3
+                           : !p->block_tables  ? 1 << 30
+                                               : (int)std::min<int64_t>(1 << 30, (chunk_wgs + p->cus - 1) / p->cus);
     auto choose_block = [&](bool share, int *mb_out, int *occ_out) -> hipError_t {
         p->share_rings = share;
         int best = 0, best_occ = 0, occ_at_best = 0;

@@ -10,7 +10,7 @@
 // multiply samples outside an output's taps by zero, which a NaN or infinity
 // turns into NaN: up to 17 outputs before and 15 after those whose taps hold it.
 // Where the fused kernel has a zero in place of such a sample (past the end of
-// its chunk), this one takes a zero too (products below).
+// its chunk), this one takes a zero too (products_again).
 //
 // Bound: HBM (each sample read and written once) and the matrix cores, whose
 // FP32 products do not run beside one another's loads well: 4186 x 16384
@@ -103,42 +103,36 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) a[kk] = ha[4 * kk];
 
-    // Products of the wave's block of 256 outputs at t0, window operands at rq, taps
-    // read again. The operand of the last K step: where the fused kernel has a zero
-    // in place of the sample that K row 3 holds, the first one past the chunk that
-    // yields the 16 outputs, a zero too. A segment at g0 walks chunks from
-    // max(g0 - lead, 0); a chunk's last outputs reach past it only if H + 1 is a
-    // multiple of 32 (= lead). That sample's tap is zero, so it matters only where
-    // it is not finite, and then all 16 outputs are not.
+    // Outputs that are not finite are formed again, a K step at a time: products of
+    // the wave's block of 256 outputs at t0 with the window operands at rq. Where
+    // the fused kernel has a zero in place of the sample that K row 3 of the last
+    // step holds, the first one past the chunk that yields the 16 outputs, it is a
+    // zero here too. A segment at g0 walks chunks from max(g0 - lead, 0); a chunk's
+    // last outputs reach past it only if H + 1 is a multiple of 32 (= lead). That
+    // sample's tap is zero, so it matters only where it is not finite, and then all
+    // 16 outputs are not. (Choosing the operand ahead of the products cost
+    // registers, 0.5-2.5 % of a call, and with taps read per block 6 %.)
     const bool reaches = ((H + 1) & 31) == 0;
-    auto products = [&](const v4f *rq, int t0) {
+    auto products_again = [&](const float *rq, int t0) {
         int me = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
         asm volatile("" : "+v"(me));   // lane values formed here: kept from above they cost registers
         const int g = me >> 4, c = me & 15;
         const float *ha = tap_lds + kTapLead + g - c;
         v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
-        constexpr int U = KS > 0 ? 1 : 4;   // (with KS > 0 rare, and so it takes few registers)
 #pragma unroll 1
-        for (int k0 = 0; k0 < ks; k0 += U) {
-            v4f four = {};
-            if constexpr (U == 4) four = rq[k0 >> 2];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int kk = k0 + u;
-                if (kk >= ks) break;
-                float r = U == 4 ? four[u] : reinterpret_cast<const float *>(rq)[kk];
-                if (kk == ks - 1 && reaches && __builtin_amdgcn_ballot_w64(!(r <= __FLT_MAX__)) != 0) {
-                    const int tb = t0 + 16 * c, lead = env_lead(H);
-                    const uint32_t n = (uint32_t)tb >> 5, len = (uint32_t)seg_len >> 5;
-                    uint32_t seg = __umulhi(n, seg_inv);   // n / len or one less
-                    if (n - seg * len >= len) ++seg;
-                    const int start = max((int)seg * seg_len - lead, 0);
-                    if (g == 3 && ((tb + lead + 16 - start) & (kChunk - 1)) == 0) r = 0.0f;
-                }
-                const v4f e = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[4 * kk], r, kk & 1 ? e1 : e0, 0, 0, 0);
-                if (kk & 1) e1 = e;
-                else e0 = e;
+        for (int kk = 0; kk < ks; ++kk) {
+            float r = rq[kk];
+            if (kk == ks - 1) {
+                const int tb = t0 + 16 * c, lead = env_lead(H);
+                const uint32_t n = (uint32_t)tb >> 5, len = (uint32_t)seg_len >> 5;
+                uint32_t seg = __umulhi(n, seg_inv);   // n / len or one less
+                if (n - seg * len >= len) ++seg;
+                const int start = max((int)seg * seg_len - lead, 0);
+                if (g == 3 && ((tb + lead + 16 - start) & (kChunk - 1)) == 0) r = 0.0f;
             }
+            const v4f e = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[4 * kk], r, kk & 1 ? e1 : e0, 0, 0, 0);
+            if (kk & 1) e1 = e;
+            else e0 = e;
         }
         return e0 + e1;
     };
@@ -167,9 +161,8 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
             // outputs o + b + q, q = 16j + i: F[i][j] = sum_m hr[m - i] r[16j + m], r = window
             // from b; lane l supplies r[16c + 4kk + g] and receives the outputs 16c + 4g ..+3
             const v4f *rq = reinterpret_cast<const v4f *>(win + g * plane + (b >> 2) + 4 * c);
-            v4f e;
+            v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
             if constexpr (KS > 0) {
-                v4f e0 = {0.0f, 0.0f, 0.0f, 0.0f}, e1 = {0.0f, 0.0f, 0.0f, 0.0f};
                 v4f r[(KS + 3) / 4];   // all reads first
 #pragma unroll
                 for (int q = 0; q < (KS + 3) / 4; ++q) r[q] = rq[q];
@@ -178,14 +171,20 @@ envelope_rows_kernel(float *__restrict__ img, const float *__restrict__ taps, in
                     if (kk & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], r[kk >> 2][kk & 3], e1, 0, 0, 0);
                     else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], r[kk >> 2][kk & 3], e0, 0, 0, 0);
                 }
-                e = e0 + e1;
-                // outputs that are not finite are formed again (a choice of the
-                // last operand before its product cost registers, 0.5-2.5 % of a call)
-                if (reaches && __builtin_amdgcn_ballot_w64(!(__builtin_fabsf(e[0]) <= __FLT_MAX__)) != 0)
-                    e = products(rq, o + b);
             } else {
-                e = products(rq, o + b);
+                for (int q = 0; 4 * q < ks; ++q) {
+                    const v4f r = rq[q];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (4 * q + u >= ks) break;
+                        if (u & 1) e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[16 * q + 4 * u], r[u], e1, 0, 0, 0);
+                        else e0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ha[16 * q + 4 * u], r[u], e0, 0, 0, 0);
+                    }
+                }
             }
+            v4f e = e0 + e1;
+            if (reaches && __builtin_amdgcn_ballot_w64(!(__builtin_fabsf(e[0]) <= __FLT_MAX__)) != 0)   // wave-uniform
+                e = products_again(reinterpret_cast<const float *>(rq), o + b);
             const int t0 = o + b;
             const int t = t0 + 16 * c + 4 * g;
             if ((reinterpret_cast<uintptr_t>(row) & 15) == 0) {   // wave-uniform
