@@ -215,3 +215,19 @@ def test_output_over_the_channels(place, dtype, monkeypatch, capfd):
                 x.copy_(xt)
                 call(x, y) if call == plan.envelope_noalloc else call(x, out=y)
                 assert torch.equal(y, want)
+
+
+def test_blocks_without_tables_do_not_depend_on_the_record(monkeypatch, capfd):
+    """Without delay tables a block can hold 64 microphones: its size follows the occupancy alone,
+    also where the record is too short to give every compute unit several workgroups."""
+    monkeypatch.setenv("DMAS_NO_DELAY_TABLE", "1")
+    _say("blocks without tables")
+    mb = {}
+    for D, T in ((240, 2048), (240, 60000)):
+        f = synth.random_frame(np.random.default_rng(9), 512, 8, T, 4)
+        f.dirs = synth.unit_vectors(np.linspace(-60, 60, D), np.zeros(D))
+        plan, log = _logged(capfd, monkeypatch, f)
+        plan.close()
+        assert log["tables"] == "none"
+        mb[T] = log["mb"]
+    assert mb[2048] == mb[60000]
