@@ -171,9 +171,10 @@ dmas_status_t dmas_plan_desc_init(dmas_plan_desc_t *desc);
  * the RF image in d_env, DMAS_DIRECT_ROOTS=0/1 whether calls on a plan with
  * tables take the signed roots while staging the channel windows instead of
  * from a root plane (a choice made only where DMAS_RING_SHARING is not set),
- * DMAS_LOG prints the plan's choices (direct: microphones per block of calls
- * without a root plane, 0 where they use one; passes: 1 or 2 kernels of an
- * envelope) and errors to stderr. */
+ * DMAS_LOG prints the plan's choices (plane_free: the calls that use no root
+ * plane, r RF images, e envelopes, n envelopes that allocate nothing; direct:
+ * their microphones per block, 0 where every call uses a plane; passes: 1 or 2
+ * kernels of an envelope) and errors to stderr. */
 dmas_status_t dmas_plan_create(const dmas_plan_desc_t *desc, dmas_plan_t *out);
 
 /* Release a plan and its device memory. NULL is a no-op. Work queued with

@@ -261,24 +261,39 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
     }
 }
 
-// Whether a single call takes the roots while staging instead of reading them
-// from a root plane (the same bits). The plane costs a launch (2-3 us) and a pool
-// allocation and free around the call (about 15 us of host time, which bounds
-// calls whose kernels are shorter than 23-33 us, depending on the box); without
-// it a sample's root is taken again in every window that holds it, work that
-// grows with the windows' elements, and every block of 16 microphones waits for
-// its loads in turn.
-// Measured over 45 frames (back to back, plane against direct): 8 microphones, 64
-// x 1024 at order 2 33.0 and 9.9 us, 19, 181 x 3001 at order 3 25.1 and 11.6, 57,
-// 78 x 4725 at order 6 29.9 and 16.9, 30, 145 x 14067 at order 3 (6.5e7 elements)
-// 32.6 and 28.1; but 58, 210 x 4619 at order 3 (1.0e8) 42.2 and 45.6, 25, 2450 x
-// 3037 at order 3 (2e8) 58.6 and 68.7, and 241, 77 x 1408 at order 5 (3.2e7, 16
-// blocks) 48.6 and 53.4.
-bool direct_roots_pay(const dmas_plan_s *p)
+// Single calls that take the roots while staging instead of reading them from a
+// root plane (the same bits). A call that takes its plane from the pool also pays
+// the pool's allocation and free: about 15 us of host time, which makes 23-33 us
+// (depending on the box) the least a call takes, and 4-5 us where the device is the
+// slower. So it takes no plane while that costs under 4 us of device time by
+// direct_extra_us; a call with the fixed scratch, which has no such cost, while it
+// saves half a us. On 660 frames of 4-128 microphones, 15-255 taps and all three
+// sums the choice was more than 3 % slower than the plane in 5 pooled envelopes, 6
+// RF images and 7 calls with the fixed scratch, at most 8 %. With the plane and
+// without: 8 microphones, 64 x 1024 at order 2 33.0 and 9.9 us, 19, 181 x 3001 at
+// order 3 25.1 and 11.6, 57, 78 x 4725 at order 6 29.9 and 16.9; but 48, 1040 x 1101
+// at order 2 with 255 taps 45.4 and 54.8, 19, 2310 x 1659 at order 8 with Kahan
+// sums 109 and 130, and with the fixed scratch 50, 3905 x 303 at order 3 31.9 and
+// 38.2.
+void choose_direct(dmas_plan_s *p, size_t lds_cap)
 {
-    const double elements =
-        (double)p->M * p->num_tiles * dmas::kDirsPerTile * p->T * (dmas::kChunk + p->range) / dmas::kChunk;
-    return p->M <= 128 && elements < 9e7;
+    if (!p->roots || !p->tables || std::getenv("DMAS_RING_SHARING")) return;
+    const char *bt = std::getenv("DMAS_BLOCK_TABLES");
+    if (bt && !p->block_tables) return;
+    if (std::max(dmas::direct_shape_of(p, true).lds_bytes, dmas::direct_shape_of(p, false).lds_bytes) > lds_cap) return;
+    auto extra = [&](bool env) {
+        int occupancy = 1;
+        if (dmas::launch_plan(p->order, nullptr, dmas::direct_shape_of(p, env && !p->two_pass), nullptr, &occupancy) !=
+            hipSuccess)
+            occupancy = 1;
+        return dmas::direct_extra_us(p, env, occupancy);
+    };
+    const double env = extra(true);
+    p->direct_env = env < 4.0;
+    p->direct_rf = extra(false) < 4.0;
+    p->direct_noalloc = env < -0.5;
+    if (const char *dr = std::getenv("DMAS_DIRECT_ROOTS"))
+        p->direct_env = p->direct_rf = p->direct_noalloc = std::atoi(dr) != 0;
 }
 
 // Whether an envelope call runs as two passes: the RF image into the output, then
@@ -515,7 +530,7 @@ dmas_status_t run(dmas_plan_t plan, const void *d_x, float *d_out, float in_scal
     hipStream_t st = static_cast<hipStream_t>(stream);
     float2 *plane = nullptr;
     bool padded = false;
-    const bool direct = dmas::call_direct(plan, d_x, d_out, env);
+    const bool direct = dmas::call_direct(plan, d_x, d_out, env, noalloc);
     hipError_t e = hipSuccess;
     if (plan->roots && noalloc) {
         const size_t need = dmas::plane_bytes(plan);
@@ -723,17 +738,12 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     // global-to-LDS loads). With Kahan or FP64 sums, whose register budgets
     // differ, the per-microphone reads one ahead stay (1.4-2.4 % faster
     // there). DMAS_BLOCK_TABLES=0/1 overrides the choice for M <= 64 (tuning).
-    // Single calls that take the roots while staging read per-block tables
-    // whatever the other launches of the plan (a server's) read.
-    p->direct = p->roots && p->tables && direct_roots_pay(p);
-    if (const char *dr = std::getenv("DMAS_DIRECT_ROOTS")) p->direct = p->roots && p->tables && std::atoi(dr) != 0;
+    // (Single calls that take the roots while staging read per-block tables
+    // whatever the other launches of the plan, a server's, read.)
     p->block_tables = M > dmas::kWaveSize || p->compensated == DMAS_ACCUM_F32;
-    if (const char *bt = std::getenv("DMAS_BLOCK_TABLES")) {
+    if (const char *bt = std::getenv("DMAS_BLOCK_TABLES"))
         p->block_tables = M > dmas::kWaveSize || std::atoi(bt) != 0;
-        p->direct = p->direct && p->block_tables;
-    }
     p->block_tables = p->block_tables && p->tables;
-    p->direct = p->direct && !std::getenv("DMAS_RING_SHARING");
     const int C = dmas::kChunk;
     const int H = (L - 1) / 2;
     // Window length. With tables a microphone's window starts at the smallest
@@ -860,9 +870,6 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     }
 
     p->direct_block = dmas::direct_block_of(mb, M, dmas::table_block_max(n));
-    if (p->direct && std::max(dmas::direct_shape_of(p, true).lds_bytes, dmas::direct_shape_of(p, false).lds_bytes) > lds_cap)
-        p->direct = false;
-
     if (p->roots) {
         double r2 = 0;   // a delay is at most the microphone's distance from the origin (triangle inequality)
         for (int i = 0; i < M; ++i) {
@@ -923,6 +930,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     }
     p->two_pass = decim == 1 && two_pass_pays(p);
     if (const char *ep = std::getenv("DMAS_ENVELOPE_PASSES")) p->two_pass = decim == 1 && std::atoi(ep) == 2;
+    choose_direct(p, lds_cap);
     if ((int64_t)p->num_tiles * std::max({p->nseg_rf, p->nseg_env, p->nseg_walk}) > INT32_MAX) {
         plan_free(p);
         return fail(DMAS_ERR_UNSUPPORTED, "grid too large");
@@ -930,11 +938,12 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     if (std::getenv("DMAS_LOG"))
         fprintf(stderr,
                 "[dmas] plan M=%d T=%d D=%d n=%d tiles=%d halo=%d range=%d row=%d mb=%d seg=%d/%d nseg=%d/%d call=%d lds=%zu/%zu "
-                "occupancy=%d/%d tables=%s direct=%d passes=%d pads=%d/%d\n",
+                "occupancy=%d/%d tables=%s direct=%d plane_free=%c%c%c passes=%d pads=%d/%d\n",
                 M, T, D, n, p->num_tiles, p->halo, p->range, p->row, p->mic_block, p->seg_walk, p->seg_env, p->nseg_walk,
                 p->nseg_env, p->seg_rf, p->lds_rf, p->lds_env, p->occ_rf, p->occ_env,
                 !p->tables ? "none" : !p->block_tables ? "mics" : p->share_rings ? "blocks,shared" : "blocks",
-                p->direct ? p->direct_block : 0, p->two_pass ? 2 : 1, p->pad0, p->pad1);
+                p->direct_rf || p->direct_env || p->direct_noalloc ? p->direct_block : 0, p->direct_rf ? 'r' : '-',
+                p->direct_env ? 'e' : '-', p->direct_noalloc ? 'n' : '-', p->two_pass ? 2 : 1, p->pad0, p->pad1);
     *out = p;
     return DMAS_OK;
 }

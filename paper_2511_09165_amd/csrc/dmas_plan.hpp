@@ -30,7 +30,9 @@ struct dmas_plan_s {
     bool cf = true, nearfield = false, linear = false;
     bool roots = false;    // kernel reads a root plane (whole-sample delays, n >= 2)
     int pad0 = 0, pad1 = 0;   // zero pairs before and after a row of single calls' root planes
-    bool direct = false;   // single calls take the roots while staging, without a root plane
+    // single calls that take the roots while staging, without a root plane: RF
+    // images, envelopes, envelopes that allocate nothing
+    bool direct_rf = false, direct_env = false, direct_noalloc = false;
     bool tables = false;   // per-tile delay tables (whole-sample delays, <= 2 GiB)
     bool block_tables = false;   // tables read a block of offsets at a time (kDelayTableBlocks)
     bool share_rings = false;    // with them, the envelope rings in the window region (...Shared)
@@ -209,8 +211,8 @@ inline LaunchShape shape_of(const dmas_plan_s *p, bool env)
     return ls;
 }
 
-// The launch of a plan with `direct` without a root plane (no rings in the
-// window region: that layout is for launches that fill the device).
+// The launch of a call without a root plane (no rings in the window region: that
+// layout is for launches that fill the device).
 inline LaunchShape direct_shape_of(const dmas_plan_s *p, bool env)
 {
     LaunchShape ls = shape_of(p, env);
@@ -251,15 +253,43 @@ void set_last_error(const char *msg);
 hipError_t launch_plan(int order, const KernelParams *kp, const LaunchShape &ls, hipStream_t st,
                        int *blocks = nullptr);
 
+// Device time in us that taking the roots while staging adds to a call of the plan
+// against reading a root plane (negative: it saves time), a fit to 220 frames of
+// 4-128 microphones at orders 2-8 with 15-255 taps (residual 2.5 us; the time
+// without a plane was 0.75 to 1.4 times that with one). Root pass and launch cost 2.4 us. A
+// workgroup waits for its loads at every block of every chunk, 0.65 us longer than
+// for copies from a plane; and a sample's root is taken again in every window that
+// holds it, 1.1 us per 1e7 window elements, with Kahan and FP64 sums 1.85.
+// occupancy: workgroups of the launch without a plane that a compute unit holds.
+inline double direct_extra_us(const dmas_plan_s *p, bool env, int occupancy)
+{
+    const bool fused = env && !p->two_pass;
+    const int seg = fused ? p->seg_env : p->seg_rf, nseg = fused ? p->nseg_env : p->nseg_rf;
+    const int H = fused ? (p->fir_len - 1) / 2 : 0, lead = fused ? env_lead(H) : 0;
+    if (nseg > 100000) return 1e9;
+    int64_t chunks = 0, longest = 0;
+    for (int s = 0; s < nseg; ++s) {
+        const int64_t g0 = (int64_t)s * seg, g1 = std::min<int64_t>(g0 + seg, p->T);
+        const int64_t n = (std::min<int64_t>(g1 + H, p->T) - std::max<int64_t>(g0 - lead, 0) + kChunk - 1) / kChunk;
+        chunks += n;
+        longest = std::max(longest, n);
+    }
+    const int64_t places = (int64_t)std::max(occupancy, 1) * std::max(p->cus, 1), workgroups = (int64_t)p->num_tiles * nseg;
+    const int64_t blocks = (p->M + p->direct_block - 1) / p->direct_block;
+    const double steps = (double)((workgroups + places - 1) / places) * (double)longest * (double)blocks;
+    const double elements = (double)p->num_tiles * p->M * (double)chunks * p->row;
+    return 0.65 * steps + (p->compensated ? 1.85e-7 : 1.1e-7) * elements - 2.4;
+}
+
 // Whether a call takes the roots while staging: the plan's choice, but not where
 // the output shares memory with the channels, which a root plane copies first.
-inline bool call_direct(const dmas_plan_s *p, const void *d_x, const float *d_out, bool env)
+inline bool call_direct(const dmas_plan_s *p, const void *d_x, const float *d_out, bool env, bool noalloc)
 {
     const size_t in = (size_t)p->M * (size_t)p->T * (p->dtype == DMAS_F32 ? 4 : 2);
     const size_t T = env ? ((size_t)p->T + p->env_decim - 1) / p->env_decim : (size_t)p->T;
     const uintptr_t x = reinterpret_cast<uintptr_t>(d_x), y = reinterpret_cast<uintptr_t>(d_out);
     const bool apart = x + in <= y || y + (size_t)p->D * T * sizeof(float) <= x;
-    return p->direct && apart;
+    return apart && (!env ? p->direct_rf : noalloc ? p->direct_noalloc : p->direct_env);
 }
 
 // Launch the beamformer of one call and, for an envelope in two passes, the

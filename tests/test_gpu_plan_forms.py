@@ -231,3 +231,25 @@ def test_blocks_without_tables_do_not_depend_on_the_record(monkeypatch, capfd):
         assert log["tables"] == "none"
         mb[T] = log["mb"]
     assert mb[2048] == mb[60000]
+
+
+# sizes where reading a root plane was measured faster (by more than a tenth) or slower
+@pytest.mark.parametrize("M,na,ne,T,n,L,accumulate,chosen", [
+    (8, 64, 1, 1024, 2, 63, "f32", "ren"),
+    (19, 181, 1, 3001, 3, 63, "f32", "ren"),
+    (19, 77, 30, 1659, 8, 63, "kahan", "---"),
+    (48, 52, 20, 1101, 2, 255, "f32", "r--"),
+    (50, 71, 55, 303, 3, 255, "f32", "--"),                      # (RF images: either)
+    (113, 10, 1, 13403, 4, 255, "f32", "--"),
+    (32, 1035, 1, 8192, 3, 63, "f32", "---"),
+])
+def test_calls_without_a_root_plane(M, na, ne, T, n, L, accumulate, chosen, monkeypatch, capfd):
+    """RF images, envelopes and envelopes that allocate nothing take the roots while staging where
+    that is the faster for each."""
+    f = synth.random_frame(np.random.default_rng(1), M, 8, T, n)
+    A, B = np.meshgrid(np.linspace(-60, 60, na), np.linspace(-30, 30, ne) if ne > 1 else [0.0])
+    f.dirs = synth.unit_vectors(A.ravel(), B.ravel())
+    plan, log = _logged(capfd, monkeypatch, f, accumulate=accumulate, fir_len=L)
+    plan.close()
+    _say(f"plane-free calls M={M} T={T} n={n} L={L} {accumulate}: {log['plane_free']}")
+    assert log["plane_free"].endswith(chosen)
