@@ -301,25 +301,28 @@ void choose_direct(dmas_plan_s *p, size_t lds_cap)
 // fused kernel's workgroups each walk long segments (a cut recomputes the
 // filter's halo), so its launch ends unevenly and starts with every workgroup
 // staging and summing in step, and its registers and rings cost occupancy; RF
-// workgroups take 1-3 chunks. Measured over 70 frames of 8-928 microphones, the
-// fused form loses about a fifth of the RF time, above order 5 three tenths, with
-// linear delays half of that (18 microphones, 1953 x 5673 at order 3: 108 against
-// 109 us in two passes). An image that the 256 MB last-level cache holds until
-// the second pass reads it costs about 0.3 ps per pixel and a launch of 4 us more
-// than the fused filter; a larger one more than the fused form loses. 64
-// microphones, 1035 x 8192 at order 3: 143 -> 99 us; 517 microphones, 361 x 4096
-// at order 2: 169 -> 116 us; 17 microphones, 6328 x 6131 at order 3: 216 -> 187
-// us; but 32 microphones, 4186 x 16384 at order 5 (274 MB): 506 -> 543 us, 14
-// microphones, 4656 x 4100 at order 2: 75 -> 85 us, and 25 microphones, 578 x
-// 6445 at order 5: 42 -> 45 us. RF launches of fewer than two workgroups per
-// compute unit are no better spread.
+// workgroups take 1-3 chunks. Measured over 490 frames of 4-928 microphones, the
+// fused form loses about a fifth of the RF time, above order 5 three tenths, or an
+// eighth for images over 64 MiB; with linear delays, and with filters of a few
+// taps, which cost the fused kernel little, half of that. An image that the 256 MB
+// last-level cache holds until the second pass reads it costs about 0.3 ps per
+// pixel and a launch of 4 us more than the fused filter; a larger one more than the
+// fused form loses. In one pass and in two: 64 microphones, 1035 x 8192 at order 3
+// 143 and 99 us; 517, 361 x 4096 at order 2 169 and 116; 17, 6328 x 6131 at order 3
+// 216 and 187; but 32, 4186 x 16384 at order 5 (274 MB) 506 and 543; 14, 4656 x 4100
+// at order 2 75 and 85; 25, 578 x 6445 at order 5 42 and 45; 18, 1953 x 5673 at order
+// 3 with linear delays 108 and 109; 12, 3552 x 8580 at order 7 173 and 189; 12, 4032
+// x 4920 at order 6 with one tap 89 and 108. RF launches of fewer than two
+// workgroups per compute unit are no better spread.
 bool two_pass_pays(const dmas_plan_s *p)
 {
     constexpr double kImageInCache = 200 << 20;
     const double pixels = (double)p->D * p->T;
     const double slots = p->order + 2 + (p->linear ? 6 : 0);           // VALU slots per microphone and pixel
     const double rf = pixels * p->M * slots / 33e12 * (p->compensated ? 2 : 1);   // seconds
-    const double loss = (p->order > 5 ? 0.3 : 0.2) * (p->linear ? 0.5 : 1.0);
+    const bool small_image = 4 * pixels <= (64 << 20);
+    const double loss = (p->order <= 5 ? 0.2 : small_image ? 0.3 : 0.12) * (p->linear ? 0.5 : 1.0) *
+                        (p->fir_len <= 7 ? 0.5 : 1.0);
     return (int64_t)p->num_tiles * p->nseg_rf >= 2 * (int64_t)p->cus && 4 * pixels <= kImageInCache &&
            loss * rf > 0.3e-12 * pixels + 4e-6;
 }

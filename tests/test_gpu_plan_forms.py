@@ -253,3 +253,23 @@ def test_calls_without_a_root_plane(M, na, ne, T, n, L, accumulate, chosen, monk
     plan.close()
     _say(f"plane-free calls M={M} T={T} n={n} L={L} {accumulate}: {log['plane_free']}")
     assert log["plane_free"].endswith(chosen)
+
+
+# sizes where one pass, or two, were measured faster by 7 % and more
+@pytest.mark.parametrize("M,na,ne,T,n,L,passes", [
+    (64, 45, 23, 8192, 3, 63, 2),
+    (17, 113, 56, 6131, 3, 63, 2),
+    (7, 74, 48, 8580, 7, 31, 1),
+    (12, 74, 48, 8580, 7, 63, 1),
+    (12, 4032, 1, 4920, 6, 1, 1),
+    (143, 70, 36, 8580, 7, 63, 2),
+])
+def test_passes_of_an_envelope(M, na, ne, T, n, L, passes, monkeypatch, capfd):
+    """The plan takes the faster of the fused filter and a pass over the image."""
+    f = synth.random_frame(np.random.default_rng(1), M, 8, T, n)
+    A, B = np.meshgrid(np.linspace(-60, 60, na), np.linspace(-30, 30, ne) if ne > 1 else [0.0])
+    f.dirs = synth.unit_vectors(A.ravel(), B.ravel())
+    plan, log = _logged(capfd, monkeypatch, f, fir_len=L)
+    plan.close()
+    _say(f"passes M={M} D={na * ne} T={T} n={n} L={L}: {log['passes']}")
+    assert int(log["passes"]) == passes
