@@ -307,13 +307,17 @@ void choose_direct(dmas_plan_s *p, size_t lds_cap)
 // taps, which cost the fused kernel little, half of that. An image that the 256 MB
 // last-level cache holds until the second pass reads it costs about 0.3 ps per
 // pixel and a launch of 4 us more than the fused filter; a larger one more than the
-// fused form loses. In one pass and in two: 64 microphones, 1035 x 8192 at order 3
-// 143 and 99 us; 517, 361 x 4096 at order 2 169 and 116; 17, 6328 x 6131 at order 3
-// 216 and 187; but 32, 4186 x 16384 at order 5 (274 MB) 506 and 543; 14, 4656 x 4100
-// at order 2 75 and 85; 25, 578 x 6445 at order 5 42 and 45; 18, 1953 x 5673 at order
-// 3 with linear delays 108 and 109; 12, 3552 x 8580 at order 7 173 and 189; 12, 4032
-// x 4920 at order 6 with one tap 89 and 108. RF launches of fewer than two
-// workgroups per compute unit are no better spread.
+// fused form loses. The second pass walks each row in steps of 2048 samples, which
+// with fewer rows than places follow one another at 1.7 us and 0.0175 us a tap each
+// (63 and 65 taps, kept in registers: 2.1); six tenths of that beyond the fused
+// filter's own matrix-core steps count as lost, the best fit: 27 microphones, 275 x
+// 21826 at order 5 with 101 taps 70 in one pass and 90 in two. In one pass and in
+// two: 64, 1035 x 8192 at order 3 143 and 99 us; 517, 361 x 4096 at order 2 169 and
+// 116; 17, 6328 x 6131 at order 3 216 and 187; but 32, 4186 x 16384 at order 5 (274
+// MB) 506 and 543; 14, 4656 x 4100 at order 2 75 and 85; 25, 578 x 6445 at order 5 42
+// and 45; 18, 1953 x 5673 at order 3 with linear delays 108 and 109; 12, 3552 x 8580
+// at order 7 173 and 189; 12, 4032 x 4920 at order 6 with one tap 89 and 108. RF
+// launches of fewer than two workgroups per compute unit are no better spread.
 bool two_pass_pays(const dmas_plan_s *p)
 {
     constexpr double kImageInCache = 200 << 20;
@@ -323,8 +327,11 @@ bool two_pass_pays(const dmas_plan_s *p)
     const bool small_image = 4 * pixels <= (64 << 20);
     const double loss = (p->order <= 5 ? 0.2 : small_image ? 0.3 : 0.12) * (p->linear ? 0.5 : 1.0) *
                         (p->fir_len <= 7 ? 0.5 : 1.0);
+    const int ks = dmas::env_ksteps((p->fir_len - 1) / 2);
+    const double walk = (double)((p->T + 2047) / 2048) * (double)((p->D + 8 * p->cus - 1) / (8 * p->cus));
+    const double steps = ((ks == 20 ? 0.6e-6 : 1.0e-6) + 0.0105e-6 * p->fir_len) * walk + 2e-6 - 5.7e-14 * ks * pixels;
     return (int64_t)p->num_tiles * p->nseg_rf >= 2 * (int64_t)p->cus && 4 * pixels <= kImageInCache &&
-           loss * rf > 0.3e-12 * pixels + 4e-6;
+           loss * rf > std::max(0.3e-12 * pixels + 4e-6, steps);
 }
 
 // Host estimate of fs*tau (tiling heuristics only; the kernels compute their own).

@@ -273,3 +273,14 @@ def test_passes_of_an_envelope(M, na, ne, T, n, L, passes, monkeypatch, capfd):
     plan.close()
     _say(f"passes M={M} D={na * ne} T={T} n={n} L={L}: {log['passes']}")
     assert int(log["passes"]) == passes
+
+
+@pytest.mark.parametrize("M,D,T,n,L,passes", [(27, 275, 21826, 5, 101, 1), (157, 153, 7406, 8, 101, 2)])
+def test_passes_of_few_long_rows(M, D, T, n, L, passes, monkeypatch, capfd):
+    """The second pass walks a row step by step: with few rows that is weighed too."""
+    f = synth.random_frame(np.random.default_rng(1), M, 8, T, n)
+    f.dirs = synth.unit_vectors(np.linspace(-60, 60, D), np.zeros(D))
+    plan, log = _logged(capfd, monkeypatch, f, fir_len=L)
+    plan.close()
+    _say(f"passes M={M} D={D} T={T} n={n} L={L}: {log['passes']}")
+    assert int(log["passes"]) == passes
