@@ -275,7 +275,17 @@ void choose_segments(int T, int num_tiles, int H, int64_t slots, int fixed, int 
 // at order 2 with 255 taps 45.4 and 54.8, 19, 2310 x 1659 at order 8 with Kahan
 // sums 109 and 130, and with the fixed scratch 50, 3905 x 303 at order 3 31.9 and
 // 38.2.
-void choose_direct(dmas_plan_s *p, size_t lds_cap)
+//
+// With Kahan and FP64 sums that launch may hold fewer workgroups per compute unit
+// than the one with a plane, and segments chosen for it come out longer. They are
+// taken, without a plane for envelopes with and without a fixed scratch, where its
+// cost, less three tenths of what the compute unit with the most chunks then has
+// fewer to sum, is under 0.5 us: 59 microphones, 96 x 8192 at order 5 with FP64 sums
+// 48 us with a plane in 516 workgroups of one chunk, of which some compute units take
+// three, and 40 without in 228 of two; served, 175 and 176. Of 200 drawn frames with
+// these sums that moved five calls with a scratch of their own (0.83-1.04 of their
+// time) and seventeen with a fixed one (0.83-0.97, one 1.08).
+void choose_direct(dmas_plan_s *p, int fixed_segment, size_t lds_cap)
 {
     if (!p->roots || !p->tables || std::getenv("DMAS_RING_SHARING")) return;
     const char *bt = std::getenv("DMAS_BLOCK_TABLES");
@@ -292,8 +302,28 @@ void choose_direct(dmas_plan_s *p, size_t lds_cap)
     p->direct_env = env < 4.0;
     p->direct_rf = extra(false) < 4.0;
     p->direct_noalloc = env < -0.5;
-    if (const char *dr = std::getenv("DMAS_DIRECT_ROOTS"))
-        p->direct_env = p->direct_rf = p->direct_noalloc = std::atoi(dr) != 0;
+    const char *dr = std::getenv("DMAS_DIRECT_ROOTS");
+    if (dr) p->direct_env = p->direct_rf = p->direct_noalloc = std::atoi(dr) != 0;
+
+    int held = 0;
+    if (!p->compensated || p->two_pass || (dr && !p->direct_env) ||
+        dmas::launch_plan(p->order, nullptr, dmas::direct_shape_of(p, true), nullptr, &held) != hipSuccess || held <= 0 ||
+        held >= p->occ_env)
+        return;
+    const int seg = p->seg_env, nseg = p->nseg_env, H = (p->fir_len - 1) / 2;
+    auto most = [&]() {   // chunks of one compute unit
+        const int chunks = (p->seg_env + H + dmas::env_lead(H) + dmas::kChunk - 1) / dmas::kChunk;
+        return (double)(((int64_t)p->num_tiles * p->nseg_env + p->cus - 1) / p->cus) * chunks;
+    };
+    const double before = most();
+    choose_segments(p->T, p->num_tiles, H, (int64_t)held * p->cus, fixed_segment, &p->seg_env, &p->nseg_env);
+    const double chunk_us = (double)dmas::kChunk * dmas::kDirsPerTile * p->M * 2 * (p->order + 2) * p->cus / 33e6;
+    if (extra(true) - 0.3 * chunk_us * (before - most()) < 0.5) {
+        p->direct_env = p->direct_noalloc = true;
+    } else {
+        p->seg_env = seg;
+        p->nseg_env = nseg;
+    }
 }
 
 // Whether an envelope call runs as two passes: the RF image into the output, then
@@ -940,7 +970,7 @@ dmas_status_t dmas_plan_create(const dmas_plan_desc_t *d, dmas_plan_t *out)
     }
     p->two_pass = decim == 1 && two_pass_pays(p);
     if (const char *ep = std::getenv("DMAS_ENVELOPE_PASSES")) p->two_pass = decim == 1 && std::atoi(ep) == 2;
-    choose_direct(p, lds_cap);
+    choose_direct(p, seg_override, lds_cap);
     if ((int64_t)p->num_tiles * std::max({p->nseg_rf, p->nseg_env, p->nseg_walk}) > INT32_MAX) {
         plan_free(p);
         return fail(DMAS_ERR_UNSUPPORTED, "grid too large");

@@ -284,3 +284,30 @@ def test_passes_of_few_long_rows(M, D, T, n, L, passes, monkeypatch, capfd):
     plan.close()
     _say(f"passes M={M} D={D} T={T} n={n} L={L}: {log['passes']}")
     assert int(log["passes"]) == passes
+
+
+@pytest.mark.parametrize("M,D,T,n,L,accumulate", [(59, 96, 8192, 5, 57, "f64"), (19, 640, 1199, 4, 63, "f64"),
+                                                  (10, 791, 12811, 3, 63, "kahan")])
+def test_segments_of_plane_free_envelopes(M, D, T, n, L, accumulate, monkeypatch, capfd):
+    """Kahan and FP64 sums: a plane-free launch that holds fewer workgroups takes longer segments;
+    the image, fresh and with a fixed scratch, and a served frame keep the plane's bits."""
+    from paper_2511_09165_amd import Server
+    f = synth.random_frame(np.random.default_rng(2), M, 8, T, n)
+    f.dirs = synth.unit_vectors(np.linspace(-60, 60, D), np.zeros(D))
+    x, got, segments = f.x_f32(), {}, {}
+    for direct in ("0", "1"):
+        monkeypatch.setenv("DMAS_DIRECT_ROOTS", direct)
+        plan, log = _logged(capfd, monkeypatch, f, accumulate=accumulate, fir_len=L)
+        segments[direct] = int(log["nseg"].split("/")[1])
+        _say(f"M={M} D={D} T={T} n={n} L={L} {accumulate} direct={direct}: {segments[direct]} segments")
+        with plan, Server(256 << 20, staging=32 << 20) as srv:
+            xt = torch.from_numpy(x).cuda()
+            t = srv.submit(plan, x)
+            srv.wait(t, 30.0)
+            out = plan.envelope(xt)
+            got[direct] = [out.cpu().numpy(), srv.fetch(t),
+                           plan.envelope_noalloc(xt, torch.full_like(out, float("nan"))).cpu().numpy()]
+            srv.release(t)
+    assert segments["1"] <= segments["0"]
+    for a in got["0"] + got["1"]:
+        np.testing.assert_array_equal(a, got["0"][0])
